@@ -218,6 +218,42 @@ struct Item {
   int32_t slot, t0, t1, pad_;
 };
 
+// A solve of the resident loop (cg_resident.hip): the vectors, state and
+// partials between two iterations exactly as the tile passes leave them before
+// an odd iteration (K_CG1, K_PCG or K_CG1F, x up to date); a launch reads them
+// and writes them back in that form, or with the solve stopped.
+struct alignas(16) ResSolve {
+  Geo g;
+  const State* st_in;
+  State* st_out;           // may be st_in
+  const double* part_in;
+  double* part_out;        // may be part_in
+  double* x;
+  double* r;
+  double* pc;              // classic: the direction
+  double* w;               // pipelined
+  double* z;
+  double* q;
+  double* p;
+  float* rf;               // refinement's inner solve
+  float* df;
+  float* pf;
+  uint64_t* sync;          // exchange area (resident_area_bytes), zero before the
+                           // solve's first launch; word 0 set: abandoned
+  uint32_t seq;            // number of this launch's first meeting, at least 1; it uses
+                           // 2 (budget + 2) numbers at most
+  int32_t budget;          // iterations of this launch at least, if the solve goes on
+                           // (one more where they would end on an odd one)
+  int32_t spin;            // polls without progress before a wait is given up
+};
+
+// Work-group `wg` of solve `solve` of a launch over several solves.
+struct ResWg {
+  int32_t solve, wg;
+};
+
+constexpr int kResMaxTiles = 1536;  // tiles of a resident solve
+
 // Fixed-point variant (cg_fixed.hip): values are Q20.30 held as int64 counts
 // of 2^-30 in [-2^49, 2^49 - 1] (the paper's 50-bit format with 20 integer
 // bits, round to nearest with ties up, saturation).  One work-group of up to
@@ -314,6 +350,17 @@ int step_op_max_blocks_per_cu(int op);
 hipError_t launch_step_cheb(int s, bool f32, const Slot* slots, const Item* items,
                             const int* cinfo, const int* step_base, int k, int grid,
                             hipStream_t st);
+// The resident loop.  kind: 0 classic FP64, 1 pipelined FP64, 2 the FP32 inner
+// solve; rows: of a strip; strips: per wavefront, hence tiles per work-group;
+// near: all work-groups of a solve on one XCD.  One solve (many null; n = ntx *
+// ceil(nty / strips) work-groups) or the n listed work-groups of several (near:
+// those of a solve in blocks of equal number modulo 8).  All must fit the
+// device, near an eighth of it, together (resident_blocks_per_cu, 0 where the
+// shape is not compiled).
+int resident_blocks_per_cu(int kind, int rows, int strips, bool near);
+hipError_t launch_resident(int kind, int rows, int strips, bool near, const ResSolve& one,
+                           const ResSolve* many, const ResWg* wgs, int n, hipStream_t st);
+size_t resident_area_bytes(int kind, const Geo& g, int strips);
 hipError_t launch_stream(int pattern, double* const* v, size_t n, double* sink, int grid,
                          hipStream_t s);
 size_t pass_algorithmic_bytes(int kind, int64_t dof);

@@ -823,8 +823,116 @@ static int chunk_iters(Ctx& c, const Work& w) {
   return std::max(2, k & ~1);
 }
 
-static int solve_tiled(Ctx& c, Work& w, const cg_problem* p, State& s) {
+// ------------------------------------------------------- resident loop --
+
+std::mutex& resident_mutex(int device) {
+  static std::mutex m[64];
+  return m[device & 63];
+}
+
+// Whether the iteration loop of a solve runs resident, and in which form.
+// Near where the solve fits one XCD (at most three work-groups a compute
+// unit), with as few strips per wavefront as that takes: measured classic, us
+// per iteration at 1 / 2 / 4 strips: 129 x 128 2.96 / 3.08 / 3.62, 300 x 190
+// 3.35 / 3.30 / 3.61, 384^2 - / 3.82 / 4.09, 512^2 - / - / 4.55; far 4.23,
+// 4.44, 4.71 and 5.28 at best.  Far: a meeting takes longer with more
+// work-groups, an iteration with more strips: at most 192 work-groups where
+// the strips allow (pipelined 384^2, 144 / 72 work-groups: 3.24 / 3.52 us;
+// classic 512^2, 256 / 128 / 64: 6.82 / 5.28 / 5.51; classic 640 x 1000, 315 /
+// 160: 7.68 / 6.32), else the most strips.
+Resident resident_of(const Ctx& c, const Plan& pl) {
+  Resident r;
+  if (!c.resident_on || c.prof || pl.wg || pl.precond || pl.vc || pl.rr_period || pl.g.plane)
+    return r;
+  if (!pl.refined && pl.fp32g) return r;  // classic FP64 pinned to 4 columns per lane
+  r.kind = pl.refined ? 2 : pl.variant;
+  if (pl.g.tiles > kResMaxTiles) return r;
+  for (int near = c.resident_near ? 1 : 0; near >= 0 && !r.wgs; --near)
+    for (int h : {1, 2, 4}) {
+      if (c.resident_strips && h != c.resident_strips) continue;
+      const int cus = near ? c.num_cu / 8 : c.num_cu;
+      const int per_cu = resident_blocks_per_cu(r.kind, pl.g.rows, h, near);
+      const int n = pl.g.ntx * ((pl.g.nty + h - 1) / h);
+      if (n > (near ? std::min(per_cu, 3) : per_cu) * cus) continue;
+      r.strips = h;
+      r.wgs = n;
+      r.near = near;
+      if (near || n <= 192) break;
+    }
+  return r;
+}
+
+ResSolve resident_solve(const Work& w, uint64_t* sync, uint32_t seq, int budget, int spin) {
+  ResSolve a;
+  memset(&a, 0, sizeof(a));
+  a.g = w.pl.g;
+  a.st_in = a.st_out = w.S[w.m & 1];
+  a.part_in = a.part_out = w.part[w.m & 1];
+  a.x = w.x;
+  a.r = w.r;
+  a.pc = w.pc[0];
+  a.w = w.w[0];
+  a.z = w.z;
+  a.q = w.q;
+  a.p = w.p;
+  a.rf = w.rf;
+  a.df = w.df;
+  a.pf = w.pf[0];
+  a.sync = sync;
+  a.seq = seq;
+  a.budget = budget;
+  a.spin = spin;
+  return a;
+}
+
+// The exchange area of a resident solve, held while it runs.
+struct ResidentArea {
+  Ctx& c;
+  Resident r;
+  uint64_t* sync = nullptr;
+  uint32_t seq = 1;
+  explicit ResidentArea(Ctx& ctx) : c(ctx) {}
+  ResidentArea(const ResidentArea&) = delete;
+  ResidentArea& operator=(const ResidentArea&) = delete;
+  ~ResidentArea() {
+    if (sync) c.arena.release(sync);
+  }
+};
+
+constexpr int kAbandoned = 1;  // run_resident: the solve is to be run by passes
+
+// Runs a solve whose next pass begins an odd iteration (K_CG1, K_PCG, K_CG1F)
+// until its state stops it.
+static int run_resident(Ctx& c, Work& w, ResidentArea& ra, State& s) {
+  std::lock_guard<std::mutex> lk(resident_mutex(c.device));
+  for (;;) {
+    const ResSolve a = resident_solve(w, ra.sync, ra.seq, c.resident_budget, c.resident_spin);
+    ra.seq += 2 * (uint32_t)(c.resident_budget + 2);
+    HIPCHK(launch_resident(ra.r.kind, w.pl.g.rows, ra.r.strips, ra.r.near, a, nullptr, nullptr,
+                           ra.r.wgs, c.st));
+    char* flag = c.host_state + 2048;  // pinned, past the state and the coefficients
+    HIPCHK(hipMemcpyAsync(flag, ra.sync, sizeof(uint64_t), hipMemcpyDeviceToHost, c.st));
+    int rc = read_state(c, w, s);
+    if (rc) return rc;
+    uint64_t dead;
+    memcpy(&dead, flag, sizeof(dead));
+    if (dead) return kAbandoned;
+    if (s.status != ST_RUNNING) return CG_OK;
+  }
+}
+
+static int solve_tiled(Ctx& c, Work& w, const cg_problem* p, State& s, bool resident = true) {
   int rc;
+  ResidentArea ra(c);
+  if (resident) {
+    ra.r = resident_of(c, w.pl);
+    if (ra.r.wgs) {
+      const size_t bytes = resident_area_bytes(ra.r.kind, w.pl.g, ra.r.strips);
+      // no room beside the solve: it runs by passes
+      ra.sync = (uint64_t*)c.arena.alloc(bytes);
+      if (ra.sync) HIPCHK(launch_fill(ra.sync, bytes, c.st));
+    }
+  }
   if (w.pl.refined) {
     // outer loop: resid -> scale -> inner chunks -> update
     HIPCHK(issue(c, w, K_RESID, [](PassArgs&) {}));
@@ -833,7 +941,9 @@ static int solve_tiled(Ctx& c, Work& w, const cg_problem* p, State& s) {
       if ((rc = read_state(c, w, s))) return rc;
       if (s.status != ST_RUNNING) break;
       w.i = 0;  // inner direction ping-pong restarts every inner solve
-      for (;;) {
+      if (ra.sync) {
+        if ((rc = run_resident(c, w, ra, s))) return rc;
+      } else for (;;) {
         // while profiling, one iteration per chunk so that at most one no-op
         // pass pair per inner solve enters the statistics
         if ((rc = run_chunk(c, w, c.prof ? 1 : chunk_iters(c, w)))) return rc;
@@ -861,7 +971,9 @@ static int solve_tiled(Ctx& c, Work& w, const cg_problem* p, State& s) {
     HIPCHK(issue(c, w, K_INIT_W, [&](PassArgs& a) { a.w_out = w.w[0]; }));
   }
   const int K = chunk_iters(c, w);
-  for (;;) {
+  if (ra.sync) {
+    if ((rc = run_resident(c, w, ra, s))) return rc;
+  } else for (;;) {
     // never issue iterations past maxit: after maxit iterations one more
     // pass only classifies the final state
     const int left = p->maxit - w.i;
@@ -977,6 +1089,11 @@ int Ctx::solve(const cg_problem* p, cg_result* res) {
        : w.pl.rr  ? solve_rr(c, w, p, s)
        : w.pl.wg  ? solve_wg(c, w, p, s)
                   : solve_tiled(c, w, p, s);
+  if (rc == kAbandoned && !w.pl.wg) {
+    // the device was not free for all of the solve's work-groups at once
+    if ((rc = stage_in(c, w, p))) return rc;
+    rc = solve_tiled(c, w, p, s, false);
+  }
   if (rc) return rc;
   if ((rc = stage_out(c, w, p, s))) return rc;
   fill_result(s, res, now_s() - t0, w.pl.refined);
@@ -1322,6 +1439,11 @@ int Ctx::init(const cg_config* cfg) {
   if (const char* e = getenv("CG_RR")) rr_enabled = atoi(e) != 0;
   if (const char* e = getenv("CG_STEP_CHUNK")) step_chunk = std::max(1, atoi(e));
   if (const char* e = getenv("CG_SERVE_CHUNK")) serve_chunk = std::max(1, atoi(e));
+  if (const char* e = getenv("CG_RESIDENT")) resident_on = atoi(e) != 0;
+  if (const char* e = getenv("CG_RESIDENT_SPIN")) resident_spin = std::max(1, atoi(e));
+  if (const char* e = getenv("CG_RESIDENT_STRIPS")) resident_strips = atoi(e);
+  if (const char* e = getenv("CG_RESIDENT_NEAR")) resident_near = atoi(e) != 0;
+  if (const char* e = getenv("CG_RESIDENT_BUDGET")) resident_budget = std::max(1, atoi(e));
   if (const char* e = getenv("CG_CHEB_ITEM_DIV")) cheb_item_div = std::max(1, atoi(e));
   load_tune_cache();
   return CG_OK;

@@ -87,8 +87,20 @@ struct Work {
   bool check = false;  // the passes being issued only classify the final state
 };
 
+// The resident loop (cg_resident.hip) of a solve: its kind, strips per
+// wavefront and work-groups; wgs == 0: the solve runs by passes.
+struct Resident {
+  int kind = 0, strips = 0, wgs = 0;
+  bool near = false;  // all work-groups on one XCD
+};
+
 struct Ctx;
 double now_s();
+Resident resident_of(const Ctx& c, const Plan& pl);
+cgk::ResSolve resident_solve(const Work& w, uint64_t* sync, uint32_t seq, int budget, int spin);
+// Held while resident launches are on the device: their work-groups wait for
+// each other, so two launches that both fit alone must not share it.
+std::mutex& resident_mutex(int device);
 bool carve(Ctx& c, Work& w);
 int stage_in(Ctx& c, Work& w, const cg_problem* p);
 cgk::State initial_state(const cg_problem* p);
@@ -132,6 +144,11 @@ struct Ctx {
   bool rr_enabled = true;      // register-resident solver for grids that fit it
   int step_chunk = 32;         // batch: steps between harvests
   int serve_chunk = 8;         // serving: steps between admissions
+  bool resident_on = true;     // iteration loops of mid-size solves in one launch
+  int resident_budget = 1024;  // ... iterations of one launch
+  int resident_spin = 1 << 20; // ... polls before a wait is given up
+  int resident_strips = 0;     // ... strips per wavefront (0: by the grid)
+  bool resident_near = true;   // ... on one XCD where it fits
   int cheb_item_div = 1;       // Chebyshev items per pass: resident work-groups / this
   int step_chunk_for(bool serving) const { return serving ? serve_chunk : step_chunk; }
   size_t engine_bytes() const {  // control block of the multi-solve engine

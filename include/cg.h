@@ -193,7 +193,9 @@ typedef struct {
  * to describe.  The tile fields always describe the
  * tile geometry of the shape (cg_dot and cg_apply use it on every path). */
 typedef struct {
-  int32_t path;             /* 0 = multi-work-group passes, 1 = single work-group,
+  int32_t path;             /* 0 = multi-work-group passes (the iterations of mid-size
+                               solves in one launch, same order and results),
+                               1 = single work-group,
                                2 = single work-group with the vectors on chip,
                                3 = fixed point, single work-group                   */
   int32_t cols_per_lane, lanes, waves, rows, threads2;

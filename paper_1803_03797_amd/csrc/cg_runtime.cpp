@@ -178,15 +178,20 @@ int Ctx::unpinned_rows(const cg_problem* p, int fp32g) const {
   return default_rows(p->nx, ny, fp32g);
 }
 
-bool Ctx::use_wg(const cg_problem* p) const {
-  return p->precision == CG_PREC_FP64 && p->precond == 0 && p->nz <= 1 && !p->kx &&
-         p->rr_period == 0 && (int64_t)p->nx * p->ny <= wg_max_dof;
-}
-
 // threads of the register-resident solver: rows of nx + 1 (one idle thread
 // per row of segments) times the segments per column
 static int64_t rr_threads_needed(int nx, int ny) {
   return (int64_t)(nx + 1) * ((ny + kRrRows - 1) / kRrRows);
+}
+
+// The tiles of a solve in one work-group: the grids of the register-resident
+// solver, where that is off.  Others iterate faster on many work-groups (us per
+// classic iteration in one / resident: 129 x 120 31.8 / 3.0, 600 x 4 13.1 / 4.9,
+// 40 x 300 40.5 / 3.1, 10 x 1500 274 / 5.1).
+bool Ctx::use_wg(const cg_problem* p) const {
+  return p->precision == CG_PREC_FP64 && p->precond == 0 && p->nz <= 1 && !p->kx &&
+         p->rr_period == 0 && rr_threads_needed(p->nx, p->ny) <= kRrThreads &&
+         (int64_t)p->nx * p->ny <= wg_max_dof;
 }
 
 bool Ctx::use_rr(const cg_problem* p) const {

@@ -192,6 +192,8 @@ struct alignas(64) Slot {
   int32_t cheb_tiles;  // partials of the Chebyshev pass
   int32_t cheb_items;  // Chebyshev items of one pass (the step's items number them)
   int32_t rr_period;   // pipelined: residual replacement every rr_period iterations; 0 none
+  int32_t hold;        // the iterations run resident: before one (an odd one, x up to
+                       // date) the step kernel only carries the solve along
   const double* cheb;  // c0, c1[s-1], c2[s-1]
   double* u;           // preconditioned pipelined: u = M^-1 r
   double* sv;          //                           s
@@ -245,7 +247,12 @@ struct alignas(16) ResSolve {
   int32_t budget;          // iterations of this launch at least, if the solve goes on
                            // (one more where they would end on an odd one)
   int32_t spin;            // polls without progress before a wait is given up
+  int32_t form;            // several solves in a launch: resident_form
 };
+
+constexpr int resident_form(int kind, int strips, bool near) {
+  return kind | strips << 4 | (near ? 256 : 0);
+}
 
 // Work-group `wg` of solve `solve` of a launch over several solves.
 struct ResWg {
@@ -352,14 +359,20 @@ hipError_t launch_step_cheb(int s, bool f32, const Slot* slots, const Item* item
                             hipStream_t st);
 // The resident loop.  kind: 0 classic FP64, 1 pipelined FP64, 2 the FP32 inner
 // solve; rows: of a strip; strips: per wavefront, hence tiles per work-group;
-// near: all work-groups of a solve on one XCD.  One solve (many null; n = ntx *
-// ceil(nty / strips) work-groups) or the n listed work-groups of several (near:
-// those of a solve in blocks of equal number modulo 8).  All must fit the
-// device, near an eighth of it, together (resident_blocks_per_cu, 0 where the
-// shape is not compiled).
+// near: all work-groups of a solve on one XCD.  One solve: n = ntx *
+// ceil(nty / strips) work-groups; several: the n listed ones (near: those of a
+// solve in blocks of equal number modulo 8).  All must fit the device, near an
+// eighth of it, together (resident_blocks_per_cu, 0 where the shape is not
+// compiled).
 int resident_blocks_per_cu(int kind, int rows, int strips, bool near);
-hipError_t launch_resident(int kind, int rows, int strips, bool near, const ResSolve& one,
-                           const ResSolve* many, const ResWg* wgs, int n, hipStream_t st);
+hipError_t launch_resident(int kind, int rows, int strips, bool near, const ResSolve& one, int n,
+                           hipStream_t st);
+// Several solves, in the forms resident_many_has; then their states (pad_ set:
+// abandoned).
+int resident_many_blocks_per_cu();
+bool resident_many_has(int kind, int rows, int strips, bool near);
+hipError_t launch_resident_many(const ResSolve* many, const ResWg* wgs, int n, hipStream_t st);
+hipError_t launch_resident_states(const ResSolve* many, int n, State* out, hipStream_t st);
 size_t resident_area_bytes(int kind, const Geo& g, int strips);
 hipError_t launch_stream(int pattern, double* const* v, size_t n, double* sink, int grid,
                          hipStream_t s);

@@ -2539,6 +2539,18 @@ __global__ __launch_bounds__(kGroup, 3) void k_step(const Slot* slots, const Ite
     if (kind == K_CHEB || kind == K_CHEBW || kind == K_CHEBF || kind == K_INIT_WU ||
         kind == K_PPCG)
       continue;
+    // a solve whose iterations run resident waits for them: its state and
+    // partials move on to the next step's parity
+    if (S.hold && (kind == K_CG1 || kind == K_PCG || kind == K_CG1F) &&
+        !((kind == K_CG1F ? s.kin : s.k) & 1)) {
+      const int T = S.g.tiles;
+      for (int t = it.t0 + (int)threadIdx.x; t < it.t1; t += kGroup) {
+        S.part[(m + 1) & 1][t] = S.part[m & 1][t];
+        S.part[(m + 1) & 1][T + t] = S.part[m & 1][T + t];
+      }
+      if (it.t0 == 0 && threadIdx.x == 0) *S.S[(m + 1) & 1] = s;
+      continue;
+    }
     if (S.cpl4) {
       switch (kind) {
         case K_INIT_R: step_item<K_INIT_R, 4>(S, it, m, s, lds, rev); break;

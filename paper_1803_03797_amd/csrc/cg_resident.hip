@@ -923,34 +923,89 @@ __device__ __forceinline__ void resident_pcg(const ResSolve* pa, int wg, char* r
     write_state(y, st, !stopped ? K_PCG : st.status == ST_ZERO_RHS ? K_DONE : K_RESID);
 }
 
-// KIND: 0 classic FP64, 1 pipelined FP64, 2 the refinement's inner solve.
-// One solve: work-group blockIdx.x, near every eighth block's (block b runs on
-// XCD b % 8); several: as listed, a negative solve leaves its block idle.
 template <int KIND, int R, int H, bool NEAR>
-__global__ __launch_bounds__(kGroup) void k_resident(ResSolve one, const ResSolve* many,
-                                                     const ResWg* wgs) {
-  __shared__ alignas(16) char raw[sizeof(ResLds<double, 2, R * H>)];
-  static_assert(sizeof(ResLds<float, 4, R * H>) <= sizeof(raw), "one size for both types");
-  // `one` is the kernel's first argument: read where it lies
-  const ResSolve* a = (const ResSolve*)__builtin_amdgcn_kernarg_segment_ptr();
-  int wg = blockIdx.x;
-  if (many) {
-    const ResWg e = wgs[blockIdx.x];
-    const int i = __builtin_amdgcn_readfirstlane(e.solve);
-    if (i < 0) return;
-    wg = __builtin_amdgcn_readfirstlane(e.wg);
-    a = many + i;
-  } else if (NEAR) {
-    if (wg & 7) return;
-    wg >>= 3;
-  }
+__device__ __forceinline__ void resident(const ResSolve* a, int wg, char* raw) {
   if constexpr (KIND == 0) resident_cg<double, 2, R, H, NEAR>(a, wg, raw);
   else if constexpr (KIND == 1) resident_pcg<R, H, NEAR>(a, wg, raw);
   else resident_cg<float, 4, R, H, NEAR>(a, wg, raw);
 }
 
-// The compiled shapes: f(kernel), or f(nullptr) where there is none.
-using Kernel = void (*)(ResSolve, const ResSolve*, const ResWg*);
+constexpr size_t lds_bytes(int nr) {
+  return nr == 2 ? sizeof(ResLds<double, 2, 2>)
+         : nr == 4 ? sizeof(ResLds<double, 2, 4>)
+         : nr == 8 ? sizeof(ResLds<double, 2, 8>) : sizeof(ResLds<double, 2, 16>);
+}
+static_assert(sizeof(ResLds<float, 4, 16>) <= lds_bytes(16) &&
+                  sizeof(ResLds<float, 4, 8>) <= lds_bytes(8) &&
+                  sizeof(ResLds<float, 4, 2>) <= lds_bytes(2),
+              "one size for both types");
+
+// KIND: 0 classic FP64, 1 pipelined FP64, 2 the refinement's inner solve.
+// One solve: work-group blockIdx.x, near every eighth block's (block b runs on
+// XCD b % 8).
+template <int KIND, int R, int H, bool NEAR>
+__global__ __launch_bounds__(kGroup) void k_resident(ResSolve one) {
+  __shared__ alignas(16) char raw[lds_bytes(R * H)];
+  int wg = blockIdx.x;
+  if (NEAR) {
+    if (wg & 7) return;
+    wg >>= 3;
+  }
+  // `one` is the kernel's only argument: read where it lies
+  resident<KIND, R, H, NEAR>((const ResSolve*)__builtin_amdgcn_kernarg_segment_ptr(), wg, raw);
+}
+
+// The forms of k_resident_many, each a function of its own (inlined side by
+// side they would share one register allocation, and spill).
+typedef __attribute__((address_space(3))) char* LdsBytes;
+
+template <int KIND, int H, bool NEAR>
+__device__ __attribute__((noinline)) void resident_call(const ResSolve* a, int wg,
+                                                        LdsBytes lds) {
+  const uint64_t p = (uint64_t)a;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)p);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32));
+  resident<KIND, 2, H, NEAR>((const ResSolve*)((uint64_t)hi << 32 | lo),
+                             __builtin_amdgcn_readfirstlane(wg), (char*)lds);
+}
+
+// Several solves, one listed work-group a block; a negative solve leaves its
+// block idle.  One kernel for all forms, so that any two work-groups fit a
+// compute unit (at most 256 registers): what the host counts by.
+__global__ __launch_bounds__(kGroup, 2) void k_resident_many(const ResSolve* many,
+                                                             const ResWg* wgs) {
+  __shared__ alignas(16) char raw[lds_bytes(8)];
+  const ResWg e = wgs[blockIdx.x];
+  const int i = __builtin_amdgcn_readfirstlane(e.solve);
+  const int wg = __builtin_amdgcn_readfirstlane(e.wg);
+  if (i < 0) return;
+  const ResSolve* a = many + i;
+  switch (__builtin_amdgcn_readfirstlane(a->form)) {
+    case resident_form(0, 1, true): return resident_call<0, 1, true>(a, wg, (LdsBytes)raw);
+    case resident_form(0, 2, true): return resident_call<0, 2, true>(a, wg, (LdsBytes)raw);
+    case resident_form(0, 4, true): return resident_call<0, 4, true>(a, wg, (LdsBytes)raw);
+    case resident_form(1, 1, true): return resident_call<1, 1, true>(a, wg, (LdsBytes)raw);
+    case resident_form(1, 2, true): return resident_call<1, 2, true>(a, wg, (LdsBytes)raw);
+    case resident_form(2, 1, true): return resident_call<2, 1, true>(a, wg, (LdsBytes)raw);
+    case resident_form(2, 2, true): return resident_call<2, 2, true>(a, wg, (LdsBytes)raw);
+    case resident_form(2, 4, true): return resident_call<2, 4, true>(a, wg, (LdsBytes)raw);
+    case resident_form(0, 4, false): return resident_call<0, 4, false>(a, wg, (LdsBytes)raw);
+    case resident_form(1, 2, false): return resident_call<1, 2, false>(a, wg, (LdsBytes)raw);
+    case resident_form(2, 4, false): return resident_call<2, 4, false>(a, wg, (LdsBytes)raw);
+  }
+}
+
+// The state each solve was left in; pad_ set: it was abandoned.
+__global__ void k_resident_states(const ResSolve* many, int n, State* out) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  State s = *many[i].st_out;
+  s.pad_ = many[i].sync[0] != 0;
+  out[i] = s;
+}
+
+// The compiled shapes of one solve.
+using Kernel = void (*)(ResSolve);
 
 template <int KIND, bool NEAR>
 Kernel kernel_h(int rows, int strips) {
@@ -981,13 +1036,36 @@ int resident_blocks_per_cu(int kind, int rows, int strips, bool near) {
   return n;
 }
 
-hipError_t launch_resident(int kind, int rows, int strips, bool near, const ResSolve& one,
-                           const ResSolve* many, const ResWg* wgs, int n, hipStream_t st) {
+int resident_many_blocks_per_cu() {
+  int n = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_resident_many, kGroup, 0) != hipSuccess)
+    return 0;
+  return n;
+}
+
+bool resident_many_has(int kind, int rows, int strips, bool near) {
+  if (rows != 2) return false;
+  if (near) return strips == 1 || strips == 2 || (strips == 4 && kind != 1);
+  return strips == (kind == 1 ? 2 : 4);
+}
+
+hipError_t launch_resident(int kind, int rows, int strips, bool near, const ResSolve& one, int n,
+                           hipStream_t st) {
   const Kernel k = kernel_of(kind, rows, strips, near);
-  if (!k || n < 1 || (!many && (one.g.rows != rows || !one.sync || one.seq < 1)))
-    return hipErrorInvalidValue;
-  const int grid = !many && near ? 8 * n : n;
-  hipLaunchKernelGGL(k, dim3(grid), dim3(kGroup), 0, st, one, many, wgs);
+  if (!k || n < 1 || one.g.rows != rows || !one.sync || one.seq < 1) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k, dim3(near ? 8 * n : n), dim3(kGroup), 0, st, one);
+  return hipGetLastError();
+}
+
+hipError_t launch_resident_many(const ResSolve* many, const ResWg* wgs, int n, hipStream_t st) {
+  if (n < 1) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_resident_many, dim3(n), dim3(kGroup), 0, st, many, wgs);
+  return hipGetLastError();
+}
+
+hipError_t launch_resident_states(const ResSolve* many, int n, State* out, hipStream_t st) {
+  if (n < 1) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_resident_states, dim3((n + 63) / 64), dim3(64), 0, st, many, n, out);
   return hipGetLastError();
 }
 

@@ -425,8 +425,16 @@ bool carve(Ctx& c, Work& w) {
   if (w.pl.il > 1 && (w.pl.variant != CG_VARIANT_PIPELINED ||
                       w.pl.il != (w.pl.precond ? 10 : 8) + (w.pl.vc ? 4 : 0)))
     return false;
-  w.mem = (char*)c.arena.alloc(w.pl.footprint);
+  // the exchange area of a resident loop comes with the workspace where the
+  // arena has room for both; without it the solve runs by passes
+  w.mem = (char*)c.arena.alloc(w.pl.footprint + w.extra);
+  if (!w.mem && w.extra) {
+    w.extra = 0;
+    w.mem = (char*)c.arena.alloc(w.pl.footprint);
+  }
   if (!w.mem) return false;
+  w.sync = w.extra ? (uint64_t*)(w.mem + w.pl.footprint) : nullptr;
+  w.seq = 1;
   char* q = w.mem;
   auto take = [&](size_t n) {
     char* r = q;
@@ -749,7 +757,7 @@ State initial_state(const cg_problem* p) {
 
 int stage_in_async(Ctx& c, Work& w, const cg_problem* p, const State* pinned) {
   const Plan& pl = w.pl;
-  HIPCHK(launch_fill(w.mem, pl.footprint, c.st));
+  HIPCHK(launch_fill(w.mem, pl.footprint + w.extra, c.st));
   const hipMemcpyKind kind = p->mem == CG_MEM_HOST ? hipMemcpyHostToDevice
                                                    : hipMemcpyDeviceToDevice;
   const size_t row = (size_t)p->nx * 8, pitch = (size_t)pl.g.pitch * 8;
@@ -767,6 +775,7 @@ int stage_in_async(Ctx& c, Work& w, const cg_problem* p, const State* pinned) {
   HIPCHK(hipMemcpyAsync(w.S[0], pinned, sizeof(State), hipMemcpyHostToDevice, c.st));
   w.m = 0;
   w.i = 0;
+  w.seq = 1;
   w.maxit = p->maxit;
   w.check = false;
   return CG_OK;
@@ -867,12 +876,14 @@ Resident resident_of(const Ctx& c, const Plan& pl) {
   return r;
 }
 
-ResSolve resident_solve(const Work& w, uint64_t* sync, uint32_t seq, int budget, int spin) {
+ResSolve resident_solve(Work& w, const State* st, const double* part, int budget, int spin) {
   ResSolve a;
   memset(&a, 0, sizeof(a));
   a.g = w.pl.g;
-  a.st_in = a.st_out = w.S[w.m & 1];
-  a.part_in = a.part_out = w.part[w.m & 1];
+  a.st_in = st;
+  a.st_out = const_cast<State*>(st);
+  a.part_in = part;
+  a.part_out = const_cast<double*>(part);
   a.x = w.x;
   a.r = w.r;
   a.pc = w.pc[0];
@@ -883,40 +894,26 @@ ResSolve resident_solve(const Work& w, uint64_t* sync, uint32_t seq, int budget,
   a.rf = w.rf;
   a.df = w.df;
   a.pf = w.pf[0];
-  a.sync = sync;
-  a.seq = seq;
+  a.sync = w.sync;
+  a.seq = w.seq;
   a.budget = budget;
   a.spin = spin;
+  w.seq += 2 * (uint32_t)(budget + 2);
   return a;
 }
-
-// The exchange area of a resident solve, held while it runs.
-struct ResidentArea {
-  Ctx& c;
-  Resident r;
-  uint64_t* sync = nullptr;
-  uint32_t seq = 1;
-  explicit ResidentArea(Ctx& ctx) : c(ctx) {}
-  ResidentArea(const ResidentArea&) = delete;
-  ResidentArea& operator=(const ResidentArea&) = delete;
-  ~ResidentArea() {
-    if (sync) c.arena.release(sync);
-  }
-};
 
 constexpr int kAbandoned = 1;  // run_resident: the solve is to be run by passes
 
 // Runs a solve whose next pass begins an odd iteration (K_CG1, K_PCG, K_CG1F)
 // until its state stops it.
-static int run_resident(Ctx& c, Work& w, ResidentArea& ra, State& s) {
+static int run_resident(Ctx& c, Work& w, const Resident& r, State& s) {
   std::lock_guard<std::mutex> lk(resident_mutex(c.device));
   for (;;) {
-    const ResSolve a = resident_solve(w, ra.sync, ra.seq, c.resident_budget, c.resident_spin);
-    ra.seq += 2 * (uint32_t)(c.resident_budget + 2);
-    HIPCHK(launch_resident(ra.r.kind, w.pl.g.rows, ra.r.strips, ra.r.near, a, nullptr, nullptr,
-                           ra.r.wgs, c.st));
+    const ResSolve a = resident_solve(w, w.S[w.m & 1], w.part[w.m & 1], c.resident_budget,
+                                      c.resident_spin);
+    HIPCHK(launch_resident(r.kind, w.pl.g.rows, r.strips, r.near, a, r.wgs, c.st));
     char* flag = c.host_state + 2048;  // pinned, past the state and the coefficients
-    HIPCHK(hipMemcpyAsync(flag, ra.sync, sizeof(uint64_t), hipMemcpyDeviceToHost, c.st));
+    HIPCHK(hipMemcpyAsync(flag, w.sync, sizeof(uint64_t), hipMemcpyDeviceToHost, c.st));
     int rc = read_state(c, w, s);
     if (rc) return rc;
     uint64_t dead;
@@ -926,18 +923,10 @@ static int run_resident(Ctx& c, Work& w, ResidentArea& ra, State& s) {
   }
 }
 
-static int solve_tiled(Ctx& c, Work& w, const cg_problem* p, State& s, bool resident = true) {
+// `r`: the form of the resident loop (w.sync set), or none.
+static int solve_tiled(Ctx& c, Work& w, const cg_problem* p, State& s, const Resident& r) {
   int rc;
-  ResidentArea ra(c);
-  if (resident) {
-    ra.r = resident_of(c, w.pl);
-    if (ra.r.wgs) {
-      const size_t bytes = resident_area_bytes(ra.r.kind, w.pl.g, ra.r.strips);
-      // no room beside the solve: it runs by passes
-      ra.sync = (uint64_t*)c.arena.alloc(bytes);
-      if (ra.sync) HIPCHK(launch_fill(ra.sync, bytes, c.st));
-    }
-  }
+  const bool resident = r.wgs > 0 && w.sync;
   if (w.pl.refined) {
     // outer loop: resid -> scale -> inner chunks -> update
     HIPCHK(issue(c, w, K_RESID, [](PassArgs&) {}));
@@ -946,8 +935,8 @@ static int solve_tiled(Ctx& c, Work& w, const cg_problem* p, State& s, bool resi
       if ((rc = read_state(c, w, s))) return rc;
       if (s.status != ST_RUNNING) break;
       w.i = 0;  // inner direction ping-pong restarts every inner solve
-      if (ra.sync) {
-        if ((rc = run_resident(c, w, ra, s))) return rc;
+      if (resident) {
+        if ((rc = run_resident(c, w, r, s))) return rc;
       } else for (;;) {
         // while profiling, one iteration per chunk so that at most one no-op
         // pass pair per inner solve enters the statistics
@@ -976,8 +965,8 @@ static int solve_tiled(Ctx& c, Work& w, const cg_problem* p, State& s, bool resi
     HIPCHK(issue(c, w, K_INIT_W, [&](PassArgs& a) { a.w_out = w.w[0]; }));
   }
   const int K = chunk_iters(c, w);
-  if (ra.sync) {
-    if ((rc = run_resident(c, w, ra, s))) return rc;
+  if (resident) {
+    if ((rc = run_resident(c, w, r, s))) return rc;
   } else for (;;) {
     // never issue iterations past maxit: after maxit iterations one more
     // pass only classifies the final state
@@ -1080,6 +1069,8 @@ int Ctx::solve(const cg_problem* p, cg_result* res) {
   Work w;
   w.pl = plan(p);
   if (w.pl.footprint > arena.size()) return CG_E_NOMEM;
+  const Resident r = resident_of(c, w.pl);
+  if (r.wgs) w.extra = resident_area_bytes(r.kind, w.pl.g, r.strips);
   if (!carve(c, w)) return CG_E_NOMEM;
   struct Release {
     Ctx& c;
@@ -1093,11 +1084,11 @@ int Ctx::solve(const cg_problem* p, cg_result* res) {
   rc = w.pl.fixed ? solve_fixed(c, w, p, s)
        : w.pl.rr  ? solve_rr(c, w, p, s)
        : w.pl.wg  ? solve_wg(c, w, p, s)
-                  : solve_tiled(c, w, p, s);
+                  : solve_tiled(c, w, p, s, r);
   if (rc == kAbandoned && !w.pl.wg) {
     // the device was not free for all of the solve's work-groups at once
     if ((rc = stage_in(c, w, p))) return rc;
-    rc = solve_tiled(c, w, p, s, false);
+    rc = solve_tiled(c, w, p, s, Resident());
   }
   if (rc) return rc;
   if ((rc = stage_out(c, w, p, s))) return rc;
@@ -1424,6 +1415,7 @@ int Ctx::init(const cg_config* cfg) {
   }
   HIPCHK(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
   HIPCHK(hipStreamCreateWithFlags(&side, hipStreamNonBlocking));
+  HIPCHK(hipStreamCreateWithFlags(&loop, hipStreamNonBlocking));
   HIPCHK(hipEventCreateWithFlags(&user_ev, hipEventDisableTiming));
   HIPCHK(hipHostMalloc((void**)&host_state, 4096, hipHostMallocDefault));
   user_stream = cfg ? (hipStream_t)cfg->stream : nullptr;
@@ -1458,6 +1450,7 @@ Ctx::~Ctx() {
   (void)hipSetDevice(device);
   if (st) (void)hipStreamSynchronize(st);
   if (side) (void)hipStreamSynchronize(side);
+  if (loop) (void)hipStreamSynchronize(loop);
   for (auto& kv : graphs) (void)hipGraphExecDestroy(kv.second);
   for (auto& pr : pending) {
     (void)hipEventDestroy(pr.a);
@@ -1467,6 +1460,7 @@ Ctx::~Ctx() {
   if (user_ev) (void)hipEventDestroy(user_ev);
   if (host_state) (void)hipHostFree(host_state);
   if (own_arena) (void)hipFree(own_arena);
+  if (loop) (void)hipStreamDestroy(loop);
   if (side) (void)hipStreamDestroy(side);
   if (st) (void)hipStreamDestroy(st);
 }

@@ -72,6 +72,9 @@ struct PendingEv {
 struct Work {
   Plan pl;
   char* mem = nullptr;
+  size_t extra = 0;          // bytes past the footprint: the resident loop's exchange area
+  uint64_t* sync = nullptr;  // ... or null, where the arena had no room for it
+  uint32_t seq = 1;          // ... the number of its next meeting
   double *b = nullptr, *x = nullptr, *r = nullptr, *w[2] = {}, *z = nullptr, *q = nullptr,
          *p = nullptr, *pc[2] = {};
   float *rf = nullptr, *df = nullptr, *pf[2] = {};
@@ -97,7 +100,9 @@ struct Resident {
 struct Ctx;
 double now_s();
 Resident resident_of(const Ctx& c, const Plan& pl);
-cgk::ResSolve resident_solve(const Work& w, uint64_t* sync, uint32_t seq, int budget, int spin);
+// The solve as it stands, for a launch of `budget` iterations; numbers its meetings.
+cgk::ResSolve resident_solve(Work& w, const cgk::State* st, const double* part, int budget,
+                             int spin);
 // Held while resident launches are on the device: their work-groups wait for
 // each other, so two launches that both fit alone must not share it.
 std::mutex& resident_mutex(int device);
@@ -131,6 +136,7 @@ struct Ctx {
   int num_cu = 256;
   hipStream_t st = nullptr;
   hipStream_t side = nullptr;  // register-resident solves of a batch, beside the steps
+  hipStream_t loop = nullptr;  // resident iteration loops of a batch, beside the steps
   hipStream_t user_stream = nullptr;
   hipEvent_t user_ev = nullptr;
   void* own_arena = nullptr;

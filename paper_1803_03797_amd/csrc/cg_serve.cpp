@@ -12,10 +12,14 @@
 // and scalars resident on the device from admission to retirement.  Solves
 // small enough for the register-resident solver take no step items: the
 // chunk that follows their admission also launches them, one work-group
-// each, on a side stream, and the next harvest waits for them.
+// each, on a side stream, and the next harvest waits for them.  Mid-size
+// solves run their iterations in the resident loop (cg_resident.hip), many
+// solves to a launch beside the steps, and take step items only for the passes
+// before and after.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <condition_variable>
 #include <cstring>
 #include <deque>
@@ -44,6 +48,9 @@ struct Job {
   double t_submit = 0.0, t_admit = 0.0, t_done = 0.0;
   Work w;
   int slot = -1;
+  enum { kStep, kLoop } mode = kStep;  // in kLoop the resident launches advance it
+  int kind = -1;   // kind of its resident loop; -1: none
+  int parity = 0;  // kLoop: state and partials lie in the buffers of this parity
   int64_t steps_cap = 0;
   bool finished = false;
   int rc = CG_PENDING;  // final status (or a negative error)
@@ -57,6 +64,9 @@ class Engine {
   explicit Engine(Ctx& c, int nslots) : c_(c), n_(std::max(1, nslots)) {}
   ~Engine() {
     if (rr_pending_) (void)hipStreamSynchronize(c_.side);
+    if (loop_ev_) (void)hipEventDestroy(loop_ev_);
+    if (step_ev_) (void)hipEventDestroy(step_ev_);
+    if (h_loop_) (void)hipHostFree(h_loop_);
     if (rr_ev_) (void)hipEventDestroy(rr_ev_);
     if (stage_ev_) (void)hipEventDestroy(stage_ev_);
     if (h_rr_idx_) (void)hipHostFree(h_rr_idx_);
@@ -114,6 +124,16 @@ class Engine {
                       hipHostMallocDefault) ||
         hipHostMalloc((void**)&h_step_, kStepRing * sizeof(int), hipHostMallocDefault))
       return CG_E_DEVICE;
+    if (c_.resident_on && !c_.prof) {
+      // two work-groups of the loop on every compute unit
+      loop_xcds_ = 8;
+      loop_room_ = resident_many_blocks_per_cu() >= 2 ? 2 * (c_.num_cu / loop_xcds_) : 0;
+      const size_t host = loop_desc_bytes() + loop_wgs_bytes() + (size_t)n_ * sizeof(State);
+      if (hipEventCreateWithFlags(&loop_ev_, hipEventDisableTiming) ||
+          hipEventCreateWithFlags(&step_ev_, hipEventDisableTiming) ||
+          hipHostMalloc((void**)&h_loop_, host, hipHostMallocDefault))
+        return CG_E_DEVICE;
+    }
     memset(h_slots_, 0, (size_t)n_ * sizeof(Slot));
     slot_job_.assign(n_, nullptr);
     grid_ = std::max(8, step_max_blocks_per_cu() * c_.num_cu);
@@ -135,7 +155,30 @@ class Engine {
     if (slot < 0) return CG_E_BUSY;
     j->w = Work();
     j->w.pl = c_.plan(&j->p);
+    j->w.extra = loop_area(j);
     if (!carve(c_, j->w)) return CG_E_NOMEM;
+    if (!j->w.sync) j->kind = -1;
+    j->mode = Job::kStep;
+    const int rc0 = stage(j, slot);
+    if (rc0) {
+      (void)hipStreamSynchronize(c_.st);
+      c_.arena.release(j->w.mem);
+      return rc0;
+    }
+    slot_job_[slot] = j;
+    j->slot = slot;
+    j->t_admit = now_s();
+    if (j->w.pl.rr) rr_new_.push_back(slot);
+    else if (j->w.pl.fixed) fx_new_.push_back(slot);
+    else ++step_jobs_;
+    ++active_;
+    dirty_ = true;
+    return CG_OK;
+  }
+
+ private:
+  // Enqueues the job's inputs, initial state and slot record.
+  int stage(Job* j, int slot) {
     // the first pass: r = b - A x (FP64) or the first outer residual
     // (refined).  The slot's pinned records stay untouched until the slot is
     // freed again, which comes after a stream synchronisation: no wait here.
@@ -155,11 +198,7 @@ class Engine {
                          hipMemcpyHostToDevice, c_.st))
         rc = CG_E_DEVICE;
     }
-    if (rc) {
-      (void)hipStreamSynchronize(c_.st);
-      c_.arena.release(j->w.mem);
-      return rc;
-    }
+    if (rc) return rc;
     Slot& S = h_slots_[slot];
     memset(&S, 0, sizeof(S));
     const Work& w = j->w;
@@ -191,6 +230,7 @@ class Engine {
     S.S[1] = w.S[1];
     S.precond = w.pl.precond;
     S.rr_period = w.pl.rr_period;
+    S.hold = j->kind >= 0;
     if (w.pl.precond) {
       S.cheb_rows = w.pl.cheb_rows;
       S.cheb_tiles = w.pl.cheb_tiles;
@@ -200,25 +240,15 @@ class Engine {
       S.sv = w.sv;
       S.mv = w.mv;
     }
-    if (hipMemcpyAsync(d_slots_ + slot, &S, sizeof(Slot), hipMemcpyHostToDevice, c_.st)) {
-      (void)hipStreamSynchronize(c_.st);
-      c_.arena.release(j->w.mem);
-      return CG_E_DEVICE;
-    }
-    slot_job_[slot] = j;
-    j->slot = slot;
-    j->t_admit = now_s();
-    if (w.pl.rr) rr_new_.push_back(slot);
-    else if (w.pl.fixed) fx_new_.push_back(slot);
-    else ++step_jobs_;
     // a bound on the passes of the solve (a guard against a solve that never
     // reaches K_DONE; it cannot trigger for a correct pass sequence)
     j->steps_cap = (int64_t)step_ + step_bound(j->p, w.pl.refined, w.pl.precond);
-    ++active_;
-    dirty_ = true;
-    return CG_OK;
+    return hipMemcpyAsync(d_slots_ + slot, &S, sizeof(Slot), hipMemcpyHostToDevice, c_.st)
+               ? CG_E_DEVICE
+               : CG_OK;
   }
 
+ public:
   // Launches `steps` steps of every resident solve: a replay of the captured
   // chunk when `steps` is the chunk length, plain launches otherwise.
   int run(int steps) {
@@ -275,7 +305,15 @@ class Engine {
       fx_new_.clear();
       rr_pending_ = true;
     }
-    if (!step_jobs_) return CG_OK;
+    bool looping = false;
+    int rc = launch_loop(looping);
+    if (rc) return rc;
+    if (step_jobs_) rc = run_steps(looping ? 4 : steps);
+    return looping ? finish_loop(rc) : rc;
+  }
+
+ private:
+  int run_steps(int steps) {
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (c_.prof) {
       e0 = c_.event();
@@ -319,6 +357,200 @@ class Engine {
     return CG_OK;
   }
 
+  // ---- the resident loop
+
+  size_t loop_desc_bytes() const { return round256((size_t)n_ * sizeof(ResSolve)); }
+  size_t loop_wgs_bytes() const {
+    return round256((size_t)loop_xcds_ * std::max(loop_room_, 1) * sizeof(ResWg));
+  }
+
+  // Work-groups of a job's loop with h strips per wavefront.
+  static int loop_wgs(const Job* j, int h) {
+    return j->w.pl.g.ntx * ((j->w.pl.g.nty + h - 1) / h);
+  }
+  // Whether the job's loop has a form with h strips that fits: on one XCD
+  // (near), or on all of them with an equal share of each.
+  bool loop_fits(const Job* j, int h, bool near) const {
+    if (!resident_many_has(j->kind, j->w.pl.g.rows, h, near)) return false;
+    const int n = loop_wgs(j, h);
+    return near ? n <= loop_room_ : (n + loop_xcds_ - 1) / loop_xcds_ <= loop_room_;
+  }
+
+  // Sets the kind of the job's loop and returns the bytes of its exchange
+  // area: the most that any of its forms needs.
+  size_t loop_area(Job* j) {
+    j->kind = -1;
+    if (!loop_room_) return 0;
+    const Resident r = resident_of(c_, j->w.pl);
+    if (!r.wgs) return 0;
+    j->kind = r.kind;
+    size_t most = 0;
+    for (int h : {1, 2, 4})
+      if (loop_fits(j, h, true) || loop_fits(j, h, false))
+        most = std::max(most, resident_area_bytes(r.kind, j->w.pl.g, h));
+    if (!most) j->kind = -1;
+    return most;
+  }
+
+  // Launches the next iterations of the solves in the loop: in order of
+  // admission, as many as the device holds at once, near where one XCD holds
+  // them.  Those that need all XCDs come first (the longest, and they would
+  // wait until the others leave room on every XCD).  Few strips per wavefront make an iteration short (300 x 190 classic
+  // on one XCD 3.3 us with one or two, 3.6 with four), many let more solves in:
+  // as many as it takes for all waiting solves to fit.
+  int launch_loop(bool& launched) {
+    loop_run_.clear();
+    std::vector<Job*> wait;
+    for (int i = 0; i < n_; ++i)
+      if (slot_job_[i] && slot_job_[i]->mode == Job::kLoop) wait.push_back(slot_job_[i]);
+    if (wait.empty()) return CG_OK;
+    auto far = [&](const Job* j) {
+      return !loop_fits(j, 1, true) && !loop_fits(j, 2, true) && !loop_fits(j, 4, true);
+    };
+    std::sort(wait.begin(), wait.end(), [&](const Job* a, const Job* b) {
+      return far(a) != far(b) ? far(a) : a->t_admit < b->t_admit;
+    });
+    int least = 1;
+    for (; least < 4; least *= 2) {
+      int64_t n = 0;
+      for (const Job* j : wait) n += loop_wgs(j, least);
+      if (n <= (int64_t)loop_xcds_ * loop_room_ * 3 / 4) break;
+    }
+    loop_mem_ = (char*)c_.arena.alloc(loop_desc_bytes() + loop_wgs_bytes() +
+                                      (size_t)n_ * sizeof(State));
+    if (!loop_mem_) {
+      // no room for the launch's tables: these solves go on by steps
+      for (Job* j : wait)
+        if (int rc = to_steps(j, false)) return rc;
+      return CG_OK;
+    }
+    ResSolve* hd = (ResSolve*)h_loop_;
+    ResWg* hw = (ResWg*)(h_loop_ + loop_desc_bytes());
+    std::vector<int> used(loop_xcds_, 0);
+    const int cells = loop_xcds_ * loop_room_;
+    for (int i = 0; i < cells; ++i) hw[i] = ResWg{-1, 0};
+    auto cell = [&](int xcd) -> ResWg& { return hw[used[xcd]++ * loop_xcds_ + xcd]; };
+    for (Job* j : wait) {
+      int h = 0;
+      bool near = false;
+      int at = 0;
+      for (int k : {1, 2, 4}) {  // near: the first that fits an XCD's free room
+        if (h || !loop_fits(j, k, true)) continue;
+        if (k < least && k < 4 && loop_fits(j, 2 * k, true)) continue;
+        at = (int)(std::min_element(used.begin(), used.end()) - used.begin());
+        if (used[at] + loop_wgs(j, k) <= loop_room_) {
+          h = k;
+          near = true;
+        }
+      }
+      for (int k : {1, 2, 4}) {
+        if (h || !far(j) || !loop_fits(j, k, false)) continue;
+        int room = 0;
+        for (int x = 0; x < loop_xcds_; ++x) room += loop_room_ - used[x];
+        if (loop_wgs(j, k) <= room) h = k;
+      }
+      if (!h) continue;  // no room this time
+      const int id = (int)loop_run_.size(), n = loop_wgs(j, h);
+      hd[id] = resident_solve(j->w, j->w.S[j->parity], j->w.part[j->parity], kLoopBudget,
+                              c_.resident_spin);
+      hd[id].form = resident_form(j->kind, h, near);
+      for (int g = 0; g < n; ++g) {
+        if (!near) at = (int)(std::min_element(used.begin(), used.end()) - used.begin());
+        cell(at) = ResWg{id, g};
+      }
+      loop_run_.push_back(j);
+    }
+    const int grid = *std::max_element(used.begin(), used.end()) * loop_xcds_;
+    if (!grid) {
+      drop_loop();
+      return CG_OK;
+    }
+    // the solves' earlier passes are complete (their states have been read):
+    // nothing on the steps' stream, which may wait for a caller's, is waited
+    // for while the device is held
+    loop_lock_ = std::unique_lock<std::mutex>(resident_mutex(c_.device));
+    const int nr = (int)loop_run_.size();
+    State* ds = (State*)(loop_mem_ + loop_desc_bytes() + loop_wgs_bytes());
+    State* hs = (State*)(h_loop_ + loop_desc_bytes() + loop_wgs_bytes());
+    if (hipMemcpyAsync(loop_mem_, h_loop_, loop_desc_bytes() + (size_t)grid * sizeof(ResWg),
+                       hipMemcpyHostToDevice, c_.loop) ||
+        launch_resident_many((const ResSolve*)loop_mem_,
+                             (const ResWg*)(loop_mem_ + loop_desc_bytes()), grid, c_.loop) ||
+        launch_resident_states((const ResSolve*)loop_mem_, nr, ds, c_.loop) ||
+        hipMemcpyAsync(hs, ds, (size_t)nr * sizeof(State), hipMemcpyDeviceToHost, c_.loop) ||
+        hipEventRecord(loop_ev_, c_.loop)) {
+      (void)hipStreamSynchronize(c_.loop);
+      drop_loop();
+      return CG_E_DEVICE;
+    }
+    launched = true;
+    return CG_OK;
+  }
+
+  void drop_loop() {
+    c_.arena.release(loop_mem_);
+    loop_mem_ = nullptr;
+    if (loop_lock_.owns_lock()) loop_lock_.unlock();
+  }
+
+  // Waits for the loop's launch, with the other solves' steps beside it (a few
+  // at a time: the next launch waits for the last of them), and moves the
+  // solves that it has brought to a stop back to the steps.
+  int finish_loop(int rc) {
+    if (step_jobs_ && rc == CG_OK) {
+      if (hipEventRecord(step_ev_, c_.st)) rc = CG_E_DEVICE;
+      while (rc == CG_OK && hipEventQuery(loop_ev_) == hipErrorNotReady) {
+        if (hipEventQuery(step_ev_) == hipSuccess) {
+          rc = run_steps(2);
+          if (rc == CG_OK && hipEventRecord(step_ev_, c_.st)) rc = CG_E_DEVICE;
+        } else {
+          std::this_thread::sleep_for(std::chrono::microseconds(20));
+        }
+      }
+    }
+    if (hipEventSynchronize(loop_ev_)) rc = CG_E_DEVICE;
+    const State* hs = (const State*)(h_loop_ + loop_desc_bytes() + loop_wgs_bytes());
+    for (size_t i = 0; i < loop_run_.size() && rc == CG_OK; ++i) {
+      Job* j = loop_run_[i];
+      if (hs[i].pad_) rc = restart(j);
+      else if (!loops(hs[i])) rc = to_steps(j, true);
+    }
+    drop_loop();
+    return rc;
+  }
+
+  // The state in which the step kernel holds a solve for the loop.
+  static bool loops(const State& s) {
+    return (s.kind == K_CG1 || s.kind == K_PCG || s.kind == K_CG1F) &&
+           !((s.kind == K_CG1F ? s.kin : s.k) & 1);
+  }
+
+  // Back to the steps, with the state where the solve's parity has it: held
+  // for the loop again (`hold`), or step by step from here on.
+  int to_steps(Job* j, bool hold) {
+    Slot& S = h_slots_[j->slot];
+    S.admit_step = step_ - j->parity;
+    S.hold = hold;
+    if (!hold) j->kind = -1;
+    j->mode = Job::kStep;
+    j->steps_cap = (int64_t)step_ + step_bound(j->p, j->w.pl.refined, j->w.pl.precond);
+    ++step_jobs_;
+    dirty_ = true;
+    return hipMemcpyAsync(d_slots_ + j->slot, &S, sizeof(Slot), hipMemcpyHostToDevice, c_.st)
+               ? CG_E_DEVICE
+               : CG_OK;
+  }
+
+  // A solve that its launch abandoned: from the start, by steps.
+  int restart(Job* j) {
+    j->kind = -1;
+    j->mode = Job::kStep;
+    ++step_jobs_;
+    dirty_ = true;
+    return stage(j, j->slot);
+  }
+
+ public:
   // Moves finished solves out: copies x back, fills the result, frees memory.
   int harvest(std::vector<Job*>& done) {
     if (!active_) return CG_OK;
@@ -328,7 +560,8 @@ class Engine {
     }
     int n = 0;
     for (int i = 0; i < n_; ++i)
-      if (slot_job_[i]) h_idx_[n++] = i;
+      if (slot_job_[i] && slot_job_[i]->mode == Job::kStep) h_idx_[n++] = i;
+    if (!n) return CG_OK;
     if (hipMemcpyAsync(d_idx_, h_idx_, (size_t)n * sizeof(int), hipMemcpyHostToDevice, c_.st) ||
         launch_gather(d_slots_, d_idx_, n, step_, d_states_, c_.st) ||
         hipMemcpyAsync(h_states_, d_states_, (size_t)n * sizeof(State), hipMemcpyDeviceToHost,
@@ -342,6 +575,14 @@ class Engine {
       const State& s = h_states_[k];
       int rc;
       if (s.kind != K_DONE) {
+        if (j->kind >= 0 && loops(s)) {
+          // held: the loop takes it from here
+          j->mode = Job::kLoop;
+          j->parity = (step_ - h_slots_[i].admit_step) & 1;
+          --step_jobs_;
+          dirty_ = true;
+          continue;
+        }
         if (step_ <= j->steps_cap) continue;
         // past its pass bound: this solve alone fails; the others go on
         rc = CG_E_DEVICE;
@@ -427,7 +668,7 @@ class Engine {
     int n = 0;
     for (int i = 0; i < n_; ++i) {
       Job* j = slot_job_[i];
-      if (!j || j->w.pl.on_side()) continue;
+      if (!j || j->w.pl.on_side() || j->mode == Job::kLoop) continue;
       const int T = j->w.pl.g.tiles;
       const int per = (T + kMaxItemsPerSolve - 1) / kMaxItemsPerSolve;
       for (int t = 0; t < T; t += per) h_items_[n++] = Item{i, t, std::min(T, t + per), 0};
@@ -546,6 +787,15 @@ class Engine {
   int* h_rr_idx_ = nullptr;
   hipEvent_t rr_ev_ = nullptr, stage_ev_ = nullptr;
   bool rr_pending_ = false;  // launched, not yet joined by a harvest
+  // the resident loop: work-groups an XCD holds at once (0: no loop), and the
+  // launch in flight (its solves, tables, and the lock of the device)
+  static constexpr int kLoopBudget = 256;  // iterations a launch
+  int loop_xcds_ = 8, loop_room_ = 0;
+  hipEvent_t loop_ev_ = nullptr, step_ev_ = nullptr;
+  char* loop_mem_ = nullptr;
+  char* h_loop_ = nullptr;
+  std::vector<Job*> loop_run_;
+  std::unique_lock<std::mutex> loop_lock_;
   int step_jobs_ = 0;        // resident solves that take step items
   int active_ = 0;
   int grid_ = 8;

@@ -65,7 +65,7 @@ MODES = [(0, cg.CG_PREC_FP64), (1, cg.CG_PREC_FP64), (0, cg.CG_PREC_FP32_REFINED
 # one tile column and many, ragged rows and columns, one strip of a tile in the
 # grid, 256 tiles and one row of tiles more, more than 1024 tiles
 SHAPES = [(129, 128), (300, 190), (257, 130), (17, 1100), (1100, 17), (130, 145), (512, 512),
-          (512, 513), (1024, 1017), (1100, 1100)]
+          (512, 513), (1024, 1017), (1100, 1100), (600, 4), (2, 4000), (1, 5121)]
 
 
 @pytest.mark.parametrize("strips", [0, 1, 2, 4])
@@ -164,3 +164,74 @@ def test_contexts_in_several_threads(torch, passes):
     assert not errors
     for a, b in zip(got, ref):
         same(a, b)
+
+
+# ------------------------------------------------ batches and serving --
+
+# classic, pipelined and refined solves of one to many work-groups, a
+# preconditioned, a 3D and a variable-coefficient one that step beside them,
+# small ones that run whole, and one too large for one XCD
+MIX = [(300, 190, 0, 0, 0), (300, 190, 1, 0, 0), (200, 180, 0, 1, 0), (129, 140, 0, 0, 0),
+       (512, 512, 1, 0, 0), (513, 300, 0, 0, 0), (700, 600, 0, 1, 0), (100, 60, 0, 0, 0),
+       (260, 260, 0, 0, 4), (17, 1100, 1, 0, 0), (1000, 37, 0, 0, 0), (900, 1000, 0, 1, 0),
+       (640, 700, 0, 0, 0), (1024, 1024, 1, 0, 0), (150, 150, 0, 1, 0), (129, 128, 1, 0, 0)]
+
+
+def mix(torch, tol=1e-6, maxit=4000):
+    bs = [rhs(torch, nx, ny, 20 + k) for k, (nx, ny, _, _, _) in enumerate(MIX)]
+    kw = [dict(tol=tol, maxit=maxit, variant=v, precision=p, precond=pc)
+          for _, _, v, p, pc in MIX]
+    return bs, kw
+
+
+@pytest.fixture(scope="module")
+def mix_alone(torch, passes):
+    bs, kw = mix(torch)
+    return [solve(torch, passes, b, **k) for b, k in zip(bs, kw)]
+
+
+def as_batch(torch, ctx, bs, kws):
+    xs = [torch.zeros_like(b) for b in bs]
+    rc, res = ctx.cg_solve_batch([cg.make_problem(b, x, b.shape[1], b.shape[0], **k)
+                                  for b, x, k in zip(bs, xs, kws)])
+    return [(r.status, r, x.cpu().numpy()) for r, x in zip(res, xs)]
+
+
+def as_served(torch, ctx, bs, kws):
+    import time
+    xs = [torch.zeros_like(b) for b in bs]
+    tickets = [ctx.cg_submit(cg.make_problem(b, x, b.shape[1], b.shape[0], **k))
+               for b, x, k in zip(bs, xs, kws)]
+    out = [None] * len(bs)
+    while any(o is None for o in out):
+        for m, t in enumerate(tickets):
+            if out[m] is None:
+                rc, r = ctx.cg_poll(t)
+                if rc != cg.CG_PENDING:
+                    out[m] = (rc, cg.cg_result.from_buffer_copy(r))
+        time.sleep(0.0005)
+    return [(rc, r, x.cpu().numpy()) for (rc, r), x in zip(out, xs)]
+
+
+@pytest.mark.parametrize("how", [as_batch, as_served])
+@pytest.mark.parametrize("env", [{}, {"CG_RESIDENT_SPIN": 1}, {"CG_STEP_CHUNK": 7,
+                                                               "CG_SERVE_CHUNK": 5}])
+def test_engine_equals_the_passes(torch, mix_alone, how, env):
+    """Many solves in the loop at once, then with every wait given up (all
+    restart by steps), then with odd chunks of steps beside it."""
+    bs, kws = mix(torch)
+    with context(arena=4 << 30, **env) as c:
+        print("engine", how.__name__, env, flush=True)
+        for got, ref in zip(how(torch, c, bs, kws), mix_alone):
+            same(got, ref)
+
+
+def test_engine_with_more_solves_than_the_device_holds(torch, passes):
+    bs = [rhs(torch, 480 + k, 500, 50 + k % 3) for k in range(20)]
+    kws = [dict(tol=1e-3, maxit=2000, variant=k % 2) for k in range(20)]
+    ref = [solve(torch, passes, b, **k) for b, k in zip(bs, kws)]
+    for arena in (4 << 30, 200 << 20):
+        with context(arena=arena) as c:
+            print("many", arena, flush=True)
+            for got, r in zip(as_batch(torch, c, bs, kws), ref):
+                same(got, r)

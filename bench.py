@@ -61,8 +61,8 @@ OP_NAMES = {"2d": "", "3d": " on the 7-point operator", "vc": " with variable co
 # changes, until the counters are taken again.
 PCG_TRAFFIC_BYTES = 1646594743
 # The same for pcg_pass of the variable-coefficient operator at 4096 x 4096
-# (128 algorithmic bytes per unknown: 96 of vectors, 32 of coefficients).
-VC_TRAFFIC_BYTES = 2161653028
+# (112 algorithmic bytes per unknown: 96 of vectors, 16 of coefficients).
+VC_TRAFFIC_BYTES = 1899238336
 # The same for pcg_pass of the 7-point operator at 256^3 (z-march tiles).
 CUBE_TRAFFIC_BYTES = 1627106949
 # Fixed point (ALU-bound): exact 50 x 50-bit products per unknown and
@@ -761,9 +761,9 @@ def bench_vc(args):
             dt2 = time.perf_counter() - t1
             tol_run = dict(status=cg.cg_status_str(rc2), iterations=r2.iterations,
                            seconds=round(dt2, 4), rel_res_true=r2.rel_res_true)
-        # each stencil pass also reads the four coefficients (32 B per unknown):
+        # each stencil pass also reads the face conductivities (16 B per unknown):
         # classic applies the stencil in both of its passes, pipelined in one
-        per_iter = BYTES_PER_ITER[name] + (32 if name == "pipelined" else 64)
+        per_iter = BYTES_PER_ITER[name] + (16 if name == "pipelined" else 32)
         out[name] = dict(GDOF_iter_s=round(dof * its / dt / 1e9, 3),
                          seconds_fixed=round(dt, 4),
                          algorithmic_GBps=round(dof * its * per_iter / dt / 1e9, 1),
@@ -786,7 +786,7 @@ def bench_vc(args):
     pk = out["pipelined"]["kernels"].get("pcg_pass")
     roof = None
     if pk:
-        per_launch = (BYTES_PER_DOF["pcg_pass"] + 32) * dof
+        per_launch = (BYTES_PER_DOF["pcg_pass"] + 16) * dof
         ach = per_launch / (pk["avg_us"] * 1e-6) / 1e9
         roof = {"bound": "hbm", "kernel": "pcg_pass (variable coefficients)",
                 "achieved": round(ach, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",

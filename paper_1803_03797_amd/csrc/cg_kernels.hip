@@ -106,12 +106,11 @@ __device__ __forceinline__ EdgeAddr edge_addr2(const Strip& s, const Geo& g) {
 //
 // OP selects the operator: 0 the 5-point stencil, 1 the 7-point one (D3
 // above), 2 the variable-coefficient 5-point one, for which the walker also
-// loads the row's four face conductivities (kc: Kc rows of the west, east,
-// south and north arrays that g.kc holds one after the other, each laid out
-// like a vector) PD rows ahead with the point data.
+// loads the row's face conductivities (handed to comp as kc: Kc rows of the
+// west, east, south and north faces) PD rows ahead with the point data.
 //
-// The walker of the 5-point operators (OP 0, and OP 2 with the row's four
-// face conductivities loaded with the point data).  With g.alt the odd
+// The walker of the 5-point operators (OP 0, and OP 2 with the row's face
+// conductivities loaded with the point data).  With g.alt the odd
 // wavefronts of a tile walk their strip from its last row up (S and N keep
 // their meaning: comp still gets rows j-1, j, j+1), so that the row between
 // two wavefronts' strips is loaded by both at about the same time: the
@@ -141,20 +140,57 @@ __device__ __forceinline__ void walk2d_dir(const Geo& g, const Strip& s, HLoad h
   auto ahead_row = [&](int r) { return up ? max(r, hlim) : min(r, hlim); };
   // point rows ahead of the walk, clamped to the strip's far end
   auto point_row = [&](int r) { return up ? max(r, s.j0) : min(r, s.j1 - 1); };
+  // Face conductivities (OP 2).  A face lies between two cells: east of a cell
+  // is west of the next, north of a row is south of the row above, so a row
+  // takes its west faces (the east ones by lane shift, the tile's last from
+  // one edge load) and the south faces of itself and of row j + 1, one of
+  // which the walk has had already.  The east and north arrays supply what
+  // the others do not hold: the last column's east faces (where the row has no
+  // padding column to hold them) and the last row's north faces.  Two arrays
+  // of four read, HIP events at 4096^2: stencil_dot 187.5 -> 129.6 us,
+  // update_norm 254.6 -> 196.8, update_norm_nx 179.6 -> 123.4, pcg_pass 390.9 ->
+  // 342.5, pcg_pass_nx 350.9 -> 308.5.
   using K = Kc<T, CPL>;
+  struct KRaw {
+    Row<T, CPL> w;  // west faces of a row
+    T we;           // the face right of the tile (lane 63)
+    Row<T, CPL> lead;  // south faces of the walk's leading row: j + 1 down, j up
+  };
   const size_t kst = (size_t)g.kcs;  // from one coefficient array to the next
-  auto kload = [&](size_t off) {
-    K k;
+  const size_t kedge = s.lane != kWave - 1 ? (size_t)s.c
+                       : s.tx + 1 < g.ntx ? (size_t)(s.ct + kWave * CPL)
+                                          : 2 * kst + s.ct + kWave * CPL - 1;
+  auto faces_s = [&](int r) {  // south faces of row r (r = ny: north of the last row)
+    Row<T, CPL> v = zrow<T, CPL>();
     if constexpr (OP == 2) {
-      const double* c0 = g.kc + off + s.c;
-      k.w = ldrow<T, CPL>(c0);
-      k.e = ldrow<T, CPL>(c0 + kst);
-      k.s = ldrow<T, CPL>(c0 + 2 * kst);
-      k.n = ldrow<T, CPL>(c0 + 3 * kst);
+      const size_t o = r < g.ny ? kst + (size_t)r * P : 3 * kst + (size_t)(g.ny - 1) * P;
+      v = ldrow<T, CPL>(g.kc + o + s.c);
+    }
+    return v;
+  };
+  auto kload = [&](int j) {
+    KRaw k;
+    if constexpr (OP == 2) {
+      const size_t off = (size_t)j * P;
+      k.w = ldrow<T, CPL>(g.kc + off + s.c);
+      k.we = g.kc[off + kedge];
+      k.lead = faces_s(up ? j : j + 1);
     }
     return k;
   };
-  K qk[OP == 2 ? PD : 1];
+  auto kmake = [&](const KRaw& r, const Row<T, CPL>& behind) {
+    K k;
+    k.w = r.w;
+#pragma unroll
+    for (int i = 0; i + 1 < CPL; ++i) k.e.e[i] = r.w.e[i + 1];
+    k.e.e[CPL - 1] = dpp<kDppWaveShl1>(r.w.e[0], r.we);
+    k.s = up ? r.lead : behind;
+    k.n = up ? behind : r.lead;
+    return k;
+  };
+  KRaw qk[OP == 2 ? PD : 1];
+  Row<T, CPL> kB;  // south faces of the leading row one step behind
+  if constexpr (OP == 2) kB = faces_s(up ? s.j1 : s.j0);
   R hB = zrow<T, CPL>();  // the row behind the walk (row jst - dir)
   {
     const int rb = jst - dir;
@@ -176,7 +212,7 @@ __device__ __forceinline__ void walk2d_dir(const Geo& g, const Strip& s, HLoad h
     q[k] = hload(ro);
     qe[k] = eload(ro);
     pt[k] = point((size_t)point_row(jst + dir * k) * P);
-    if constexpr (OP == 2) qk[k] = kload((size_t)point_row(jst + dir * k) * P);
+    if constexpr (OP == 2) qk[k] = kload(point_row(jst + dir * k));
   }
   for (int j = jst; j != jen; j += dir) {
     const size_t o = (size_t)j * P;
@@ -187,8 +223,13 @@ __device__ __forceinline__ void walk2d_dir(const Geo& g, const Strip& s, HLoad h
     const RawH hn = hload(ho);
     const RawE en = eload(ho);
     const B pn = point((size_t)point_row(j + dir * PD) * P);
-    K kn;
-    if constexpr (OP == 2) kn = kload((size_t)point_row(j + dir * PD) * P);
+    KRaw kn;
+    K kc;
+    if constexpr (OP == 2) {
+      kn = kload(point_row(j + dir * PD));
+      kc = kmake(qk[0], kB);
+      kB = qk[0].lead;
+    }
     // row j + dir enters the window
     R hA = hmake(q[0]);
     T eA = emake(qe[0]);
@@ -200,8 +241,8 @@ __device__ __forceinline__ void walk2d_dir(const Geo& g, const Strip& s, HLoad h
     west_east<T, CPL>(hC, eC, eC, W, E);
     const R zr = zrow<T, CPL>();
     // S is row j - 1 and N row j + 1 in either direction
-    if (up) comp(o, hA, hC, hB, W, E, zr, zr, qk[0], pt[0]);
-    else comp(o, hB, hC, hA, W, E, zr, zr, qk[0], pt[0]);
+    if (up) comp(o, hA, hC, hB, W, E, zr, zr, kc, pt[0]);
+    else comp(o, hB, hC, hA, W, E, zr, zr, kc, pt[0]);
     hB = hC;
     hC = hA;
     eC = eA;

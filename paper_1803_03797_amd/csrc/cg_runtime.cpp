@@ -409,8 +409,9 @@ hipError_t Ctx::pass(int kind, int fp32g, const PassArgs& a, int grid, bool chec
   (void)hipEventRecord(e0, st);
   hipError_t rc = launch_pass(kind, fp32g, a, grid, st);
   (void)hipEventRecord(e1, st);
-  // the variable-coefficient operator also reads its four coefficients per
-  // unknown in every pass that applies it
+  // the variable-coefficient operator counts its four coefficients per unknown
+  // in every pass that applies it (the passes read each face once, 16 bytes an
+  // unknown: the rows share theirs)
   const int64_t dof = (int64_t)a.g.nx * a.g.ny;
   const double kc_bytes = a.g.kc && kind != K_DOT ? 32.0 * (double)dof : 0.0;
   pending.push_back({e0, e1, check ? "final_check" : kind_name(kind, fp32g),
@@ -463,7 +464,7 @@ bool carve(Ctx& c, Work& w) {
     w.q = vec();
     w.p = vec();
     if (pl.vc) {
-      w.kc = vec();  // west; east, south and north follow, width apart
+      w.kc = vec();  // west; south, east and north follow, width apart
       k += 3;
     }
     if (pl.precond) w.cheb = (double*)take(256);
@@ -764,12 +765,14 @@ int stage_in_async(Ctx& c, Work& w, const cg_problem* p, const State* pinned) {
   HIPCHK(hipMemcpy2DAsync(w.b, pitch, p->b, row, row, rows_of(p), kind, c.st));
   if (p->x0) HIPCHK(hipMemcpy2DAsync(w.x, pitch, p->x0, row, row, rows_of(p), kind, c.st));
   if (pl.vc) {
-    // cell arrays of the face conductivities: west kx[j][i], east kx[j][i+1],
-    // south ky[j][i], north ky[j+1][i] (padding stays zero from the fill)
+    // cell arrays of the face conductivities: west kx[j][i] (and kx[j][nx] in
+    // the first padding column, where there is one), south ky[j][i], east
+    // kx[j][i+1], north ky[j+1][i] (padding stays zero from the fill)
     const size_t one = (size_t)pl.g.kcs, rx = (size_t)(p->nx + 1) * 8;
-    HIPCHK(hipMemcpy2DAsync(w.kc, pitch, p->kx, rx, row, p->ny, kind, c.st));
-    HIPCHK(hipMemcpy2DAsync(w.kc + one, pitch, p->kx + 1, rx, row, p->ny, kind, c.st));
-    HIPCHK(hipMemcpy2DAsync(w.kc + 2 * one, pitch, p->ky, row, row, p->ny, kind, c.st));
+    HIPCHK(hipMemcpy2DAsync(w.kc, pitch, p->kx, rx, p->nx < pl.width ? rx : row, p->ny, kind,
+                            c.st));
+    HIPCHK(hipMemcpy2DAsync(w.kc + one, pitch, p->ky, row, row, p->ny, kind, c.st));
+    HIPCHK(hipMemcpy2DAsync(w.kc + 2 * one, pitch, p->kx + 1, rx, row, p->ny, kind, c.st));
     HIPCHK(hipMemcpy2DAsync(w.kc + 3 * one, pitch, p->ky + p->nx, row, row, p->ny, kind, c.st));
   }
   HIPCHK(hipMemcpyAsync(w.S[0], pinned, sizeof(State), hipMemcpyHostToDevice, c.st));

@@ -81,7 +81,7 @@ struct Work {
   float* zf = nullptr;  // refinement, preconditioned: z = M^-1 r_in
   double* cheb = nullptr;  // preconditioner coefficients (c0, c1[s-1], c2[s-1])
   double *u = nullptr, *sv = nullptr, *mv = nullptr;  // preconditioned pipelined
-  double* kc = nullptr;  // variable coefficients: west, east, south, north arrays
+  double* kc = nullptr;  // variable coefficients: west, south, east, north arrays
   double* part[2] = {};
   cgk::State* S[2] = {};
   int m = 0;  // passes issued (state/partial parity)

@@ -311,3 +311,26 @@ def test_profiled_passes(ctx):
         for name, per, launches in passes:
             assert st[name]["launches"] == launches, (name, st[name])
             assert st[name]["bytes"] == launches * per * n * n, (name, st[name])
+
+
+@pytest.mark.parametrize("variant", VARIANTS)
+@pytest.mark.parametrize("nx,ny,rows", [(128, 5, 0), (127, 9, 0), (256, 70, 0), (255, 130, 0),
+                                        (129, 33, 1), (384, 1, 0), (256, 40, 1), (128, 64, 16)])
+def test_faces_shared_between_cells(ctx, nx, ny, rows, variant):
+    """A row's east faces are its west ones shifted and its north faces the
+    next row's south ones: rows without a padding column, with one, tile
+    columns that end at the grid, strips of one row, of the grid's last."""
+    kx, ky = faces(nx, ny, 11 * nx + ny)
+    b = np.random.default_rng(nx + 5 * ny).uniform(-1, 1, (ny, nx))
+    if rows:
+        ctx.cg_pin_tile(nx, ny, rows)
+    o = tile_order(ctx, nx, ny, variant)
+    for m in (1, 2, 5):
+        say("vc shared faces", nx, ny, "rows", rows, "variant", variant, "maxit", m)
+        x = np.zeros_like(b)
+        rc, res = ctx.solve(b, x, nx, ny, tol=0.0, maxit=m, variant=variant, kx=kx, ky=ky)
+        xo, ro = oracle.cg_vc(b, nx, ny, kx, ky, variant=variant, tol=0.0, maxit=m,
+                              mode=MODE_CANONICAL, order=o)
+        assert rc == ro.status and res.iterations == ro.iterations
+        np.testing.assert_array_equal(x, xo)
+        assert res.rel_res_true == ro.rel_res_true

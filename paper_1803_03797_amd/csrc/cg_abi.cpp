@@ -131,7 +131,7 @@ int cg_plan(cg_ctx* ctx, const cg_problem* prob, cg_plan_info* info) {
   cgr::Plan pl = c->plan(&q);
   memset(info, 0, sizeof(*info));
   info->path = pl.fixed ? 3 : pl.rr ? 2 : pl.wg ? 1 : 0;
-  info->seg_rows = pl.rr ? cgk::kRrRows : 0;
+  info->seg_rows = pl.rr ? pl.rr_rows : 0;
   info->seg_waves = pl.rr ? pl.rr_threads / cgk::kWave : 0;
   info->seg_cols = pl.rr ? prob->nx + 1 : 0;
   info->cols_per_lane = pl.fp32g ? 4 : 2;

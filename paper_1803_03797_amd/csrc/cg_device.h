@@ -195,31 +195,48 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-// The same butterfly (stage order 32, 16, ..., 1; every lane adds its xor
-// partner) with the stages inside 32-lane halves done by DPP row/quad
-// permutations (xor 8, 2, 1) or ds_swizzle (xor 16, 4), whose lane patterns
-// are immediates: no per-lane address registers, half the LDS round trips.
-template <int M>
-__device__ __forceinline__ double swz_xor(double v) {
-  constexpr int pat = 0x1f | (M << 10);  // bitmask mode: lane ^ M within 32 lanes
-  const int lo = __builtin_amdgcn_ds_swizzle(__double2loint(v), pat);
-  const int hi = __builtin_amdgcn_ds_swizzle(__double2hiint(v), pat);
-  return __hiloint2double(hi, lo);
-}
-
 // DPP controls that are xor permutations inside 16-lane rows.
 constexpr int kDppXor8 = 0x128;  // row_ror:8: lane l of a 16-lane row gets lane l ^ 8
 constexpr int kDppXor2 = 0x4E;   // quad_perm [2,3,0,1]: lane l gets lane l ^ 2
 constexpr int kDppXor1 = 0xB1;   // quad_perm [1,0,3,2]: lane l gets lane l ^ 1
 
-__device__ __forceinline__ double wave_sum_swz(double v) {
-  v = v + __shfl_xor(v, 32, kWave);
-  v = v + swz_xor<16>(v);
-  v = v + dpp<kDppXor8>(v, v);
-  v = v + swz_xor<4>(v);
-  v = v + dpp<kDppXor2>(v, v);
-  v = v + dpp<kDppXor1>(v, v);
+// The butterfly of wave_sum (stage order 32, 16, ..., 1; addition commutes)
+// without LDS: xor 32 and 16 by gfx950's lane swaps, 8, 4, 2 and 1 by DPP.
+__device__ __forceinline__ double swap_add32(double v) {
+  const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+  const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+__device__ __forceinline__ double swap_add16(double v) {
+  const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+  const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+constexpr int kDppHalfMirror = 0x141;  // lane l of 8 gets lane l ^ 7
+constexpr int kDppXor3 = 0x1B;         // quad_perm [3,2,1,0]: lane l gets lane l ^ 3
+
+// A lane permutation that every lane takes part in.
+template <int CTRL>
+__device__ __forceinline__ double perm(double v) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+
+__device__ __forceinline__ double wave_sum_valu(double v) {
+  v = swap_add32(v);
+  v = swap_add16(v);
+  v = v + perm<kDppXor8>(v);
+  v = v + perm<kDppXor3>(perm<kDppHalfMirror>(v));  // l ^ 7 ^ 3 = l ^ 4
+  v = v + perm<kDppXor2>(v);
+  v = v + perm<kDppXor1>(v);
   return v;
+}
+
+__device__ __forceinline__ bool uniform_flag(bool b) {
+  return __builtin_amdgcn_readfirstlane((int)b) != 0;
 }
 
 // ------------------------------------------------------- tile geometry --
@@ -631,6 +648,14 @@ __device__ __forceinline__ bool transition_x(State& s, const double* sum, Sc& sc
     }
   }
   return run;
+}
+
+// A barrier that orders LDS only: global stores in flight (the exchange words)
+// are not waited for.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // ------------------------------------------------------------- reductions --

@@ -21,7 +21,7 @@ constexpr int kWave = 64;
 constexpr int kGroup = 256;       // threads that process one tile (4 wavefronts)
 constexpr int kWavesPerTile = 4;
 constexpr int kWgGroups = 2;     // tile groups of the single-work-group solver
-constexpr int kRrRows = 20;       // rows per thread of the register-resident solver
+constexpr int kRrRows = 20;       // most rows per thread of the register-resident solver
 constexpr int kRrThreads = 512;   // its largest work-group
 constexpr int kChebMaxSteps = 8;  // Chebyshev preconditioner steps (halo s - 1)
 
@@ -297,14 +297,39 @@ struct FxArgs {
   State* S[2];      // tol and maxit in S[0]; the final state lands in both
 };
 
-// Host-side launchers (cg_kernels.hip, cg_fixed.hip).
+// The on-chip solver (cg_onchip.hip): threads it takes with `rows` rows a thread
+// (rows of nx + 1 threads, one of them idle, a row for each segment of the
+// columns), and the rows it takes for a grid (0: too large).  The fewest that
+// fit: an iteration costs a fixed 1.3 us and about 0.07 us for each row a thread
+// holds (64 x 64 classic: 1.8 us with 10 rows, 4.2 with 20 on half the
+// wavefronts).  At most four forms, each compiled with its rows in registers.
+__host__ __device__ inline int64_t rr_threads(int nx, int ny, int rows) {
+  return (int64_t)(nx + 1) * ((ny + rows - 1) / rows);
+}
+__host__ __device__ inline int rr_rows(int nx, int ny) {
+  return rr_threads(nx, ny, 2) <= kRrThreads    ? 2
+         : rr_threads(nx, ny, 5) <= kRrThreads  ? 5
+         : rr_threads(nx, ny, 10) <= kRrThreads ? 10
+         : rr_threads(nx, ny, kRrRows) <= kRrThreads ? kRrRows : 0;
+}
+
+struct RrArgs {
+  Geo g;             // nx, ny, pitch
+  const double* b;
+  const double* x0;  // null: zeros; may be x
+  double* x;
+  State s0;
+  State* out;        // final state (device or pinned host memory)
+};
+
+// Host-side launchers (cg_kernels.hip, cg_onchip.hip, cg_fixed.hip).
 hipError_t launch_pass(int kind, int fp32_geometry, const PassArgs& a, int grid, hipStream_t s);
 hipError_t launch_final(const PassArgs& a, hipStream_t s);  // res2 = sum of slot 0
 hipError_t launch_fill(void* p, size_t bytes, hipStream_t s);
 hipError_t launch_solve_wg(int variant, const PassArgs& a, hipStream_t s);
 // Whole solve in one work-group of `threads` threads with the vectors on chip;
-// needs (nx + 1) * ceil(ny / kRrRows) <= threads <= kRrThreads.
-hipError_t launch_solve_rr(int variant, const PassArgs& a, int threads, hipStream_t s);
+// needs rr_threads(nx, ny, rr_rows(nx, ny)) <= threads <= kRrThreads.
+hipError_t launch_solve_rr(int variant, const RrArgs& a, int threads, hipStream_t s);
 // One register-resident solve per listed slot (slots[idx[i]], i < n), each
 // fitting the solver; final states land in both state buffers, kind K_DONE.
 hipError_t launch_solve_rr_many(const Slot* slots, const int* idx, int n, hipStream_t s);

@@ -1925,474 +1925,6 @@ __global__ __launch_bounds__(kWgGroups * kGroup) void k_solve_wg(PassArgs a0) {
   if (threadIdx.x == 0) *a0.st_out = s;
 }
 
-// ------------------------------------------ register-resident small solve --
-//
-// For a grid with (nx + 1) * ceil(ny / kRrRows) <= kRrThreads the whole solve
-// runs in one work-group with every vector on chip.  Threads are laid out in
-// rows of nx + 1: thread t owns column c = t mod (nx + 1) and the kRrRows rows
-// of segment t div (nx + 1) (rows past ny are held as zero); the last thread
-// of each row (c == nx) and the threads past the last segment own nothing and
-// hold zeros, so the west neighbour of column 0 and the east neighbour of
-// column nx-1 read as zero without a test.  Along a column the stencil's
-// south/north neighbours are the thread's own registers; west/east neighbours
-// come from the adjacent lanes by DPP.  What crosses a thread's boundary (the
-// first and last element of every segment, the whole segment of lanes 0 and
-// 63 of each wavefront) goes through LDS, together with the wavefront sums of
-// the dot products, with one barrier per exchange and the LDS buffers
-// double-buffered by phase parity.  Pipelined CG keeps x in LDS (six vectors
-// do not fit the register file), classic CG keeps all four of its vectors
-// (x, r, p, A p) in registers.
-//
-// Rows outside the grid hold exact zeros through every update (the stencil
-// result is forced to zero there, and every other update maps zeros to +0),
-// so the dot products accumulate them without a test: fma(0, 0, acc) == acc.
-//
-// Dot products follow the column-segment order: fma per thread over its rows
-// in ascending order, xor butterfly, wavefronts in order.  The scalar
-// recurrences are the transitions of the pass kernels, and every vector
-// update is the same expression as in the pass bodies.
-
-constexpr int kRrWaves = kRrThreads / kWave;
-
-struct RrXchg {  // one exchanged vector
-  double first[kRrThreads];  // element 0 of each thread's segment
-  double last[kRrThreads];   // element kRrRows-1
-  // segments of lanes 0 and 63 of wavefront w at [w + 1]; [0] stays zero (the
-  // west neighbour of thread 0)
-  double edge[kRrWaves + 1][2][kRrRows];
-};
-
-struct RrLdsPcg {
-  RrXchg x[2];                     // by phase parity
-  double tot[2][kRrWaves][2];      // wavefront sums, by phase parity
-  double xs[kRrRows][kRrThreads];  // the iterate x
-};
-
-struct RrLdsCg {
-  RrXchg x[2][2];  // [parity][r, p]
-  double tot[2][kRrWaves][2];
-};
-
-constexpr size_t kRrLdsBytes =
-    sizeof(RrLdsPcg) > sizeof(RrLdsCg) ? sizeof(RrLdsPcg) : sizeof(RrLdsCg);
-
-struct RrSeg {
-  int t, lane, wave, nw;
-  int stride;         // threads per row of segments (nx + 1)
-  int nv;             // rows of the segment inside the grid (0: idle thread)
-  bool south, north;  // the segment below / above exists
-  size_t off;         // element offset of the segment's first row (padded pitch)
-  int pitch;
-};
-
-__device__ __forceinline__ RrSeg rr_seg(const Geo& g) {
-  RrSeg s;
-  s.t = threadIdx.x;
-  s.lane = s.t & (kWave - 1);
-  s.wave = s.t >> 6;
-  s.nw = blockDim.x >> 6;
-  s.stride = g.nx + 1;
-  const int nseg = (g.ny + kRrRows - 1) / kRrRows;
-  const int c = s.t % s.stride, sg = s.t / s.stride;
-  const bool act = sg < nseg && c < g.nx;
-  s.nv = act ? min(kRrRows, g.ny - sg * kRrRows) : 0;
-  s.south = act && sg > 0;
-  s.north = act && sg + 1 < nseg;
-  s.pitch = g.pitch;
-  s.off = act ? (size_t)sg * kRrRows * g.pitch + c : 0;
-  return s;
-}
-
-// Zeroes the never-written edge entry of both parities of an exchange buffer.
-__device__ __forceinline__ void rr_clear_edge0(RrXchg& X) {
-  const int t = threadIdx.x;
-  if (t < 2 * kRrRows) X.edge[0][t / kRrRows][t % kRrRows] = 0.0;
-}
-
-using RrVec = double[kRrRows];
-
-// The segment's addresses are recomputed at every use (the empty asm hides
-// the offset from common-subexpression elimination), so the addresses of the
-// first load are not kept in registers across the whole solve.
-__device__ __forceinline__ void rr_load(const double* G, const RrSeg& s, RrVec& v) {
-  size_t off = s.off;
-  asm volatile("" : "+v"(off));
-#pragma unroll
-  for (int e = 0; e < kRrRows; ++e) v[e] = e < s.nv ? G[off + (size_t)e * s.pitch] : 0.0;
-}
-
-__device__ __forceinline__ void rr_store(double* G, const RrSeg& s, const RrVec& v) {
-  size_t off = s.off;
-  asm volatile("" : "+v"(off));
-#pragma unroll
-  for (int e = 0; e < kRrRows; ++e)
-    if (e < s.nv) G[off + (size_t)e * s.pitch] = v[e];
-}
-
-// After a transition: the state and the pass scalars back in scalar registers.
-__device__ __forceinline__ void rr_uniform(State& st, Sc& sc) {
-  st = uniform_state(st);
-  sc.al = uniform(sc.al);
-  sc.be = uniform(sc.be);
-}
-
-__device__ __forceinline__ void rr_publish(const RrVec& v, const RrSeg& s, RrXchg& X) {
-  X.first[s.t] = v[0];
-  X.last[s.t] = v[kRrRows - 1];
-  if (s.lane == 0 || s.lane == kWave - 1) {
-    double* d = X.edge[s.wave + 1][s.lane == 0 ? 0 : 1];
-#pragma unroll
-    for (int e = 0; e < kRrRows; ++e) d[e] = v[e];
-  }
-}
-
-// Neighbour values of a published vector just outside this thread's segment:
-// south of element 0 and north of element kRrRows-1 (from the segments below
-// and above), and for lanes 0 / 63 the west / east neighbours from the
-// adjacent wavefront.  `f` maps the published values to the vector the
-// stencil is applied to (identity, or the classic direction update); X2 is a
-// second published vector that f combines with the first.
-template <class F>
-struct RrHalo {
-  double S, N;
-  // the wavefront's west edge (used by lane 0) and east edge (used by lane
-  // 63); wavefront-uniform addresses, so every lane reads the same entry
-  const double *eW, *eE;
-  const double *eW2, *eE2;
-  F f;
-};
-
-template <class F>
-__device__ __forceinline__ RrHalo<F> rr_halo(const RrSeg& s, const RrXchg& X, const RrXchg* X2,
-                                             F f) {
-  const int ts = s.south ? s.t - s.stride : s.t, tn = s.north ? s.t + s.stride : s.t;
-  const double S = f(X.last[ts], X2 ? X2->last[ts] : 0.0);
-  const double N = f(X.first[tn], X2 ? X2->first[tn] : 0.0);
-  // west: lane 63 of the previous wavefront (the zero entry for wavefront 0);
-  // east: lane 0 of the next (for the last wavefront an entry nobody uses)
-  const int ww = s.wave, we = min(s.wave + 2, s.nw);
-  return RrHalo<F>{s.south ? S : 0.0,
-                   s.north ? N : 0.0,
-                   X.edge[ww][1],
-                   X.edge[we][0],
-                   X2 ? X2->edge[ww][1] : nullptr,
-                   X2 ? X2->edge[we][0] : nullptr,
-                   f};
-}
-
-// (A v) at element e of the segment; zero for rows outside the grid.  vs is
-// v[e-1] as it was before any update of this pass (the caller may have
-// overwritten v[e-1] already); unused for e == 0.
-template <class F>
-__device__ __forceinline__ double rr_st5(const RrVec& v, double vs, const RrSeg& s,
-                                         const RrHalo<F>& h, int e) {
-  const double evW = h.f(h.eW[e], h.eW2 ? h.eW2[e] : 0.0);
-  const double evE = h.f(h.eE[e], h.eE2 ? h.eE2[e] : 0.0);
-  const double w = dpp<kDppWaveShr1>(v[e], evW);   // lane 0 keeps its west edge
-  const double ea = dpp<kDppWaveShl1>(v[e], evE);  // lane 63 keeps its east edge
-  const double so = e > 0 ? vs : h.S;
-  const double no = e + 1 < kRrRows ? v[e + 1] : h.N;
-  return e < s.nv ? st5(v[e], w, ea, so, no) : 0.0;
-}
-
-template <int D>
-__device__ __forceinline__ void rr_publish_sums(const double* acc, const RrSeg& s,
-                                                double (*tot)[2]) {
-#pragma unroll
-  for (int d = 0; d < D; ++d) {
-    const double v = wave_sum_swz(acc[d]);
-    if (s.lane == 0) tot[s.wave][d] = v;
-  }
-}
-
-// Sums of the wavefront totals in wavefront order.  All kRrWaves entries are
-// loaded at once (entries of absent wavefronts are read but not added).
-template <int D>
-__device__ __forceinline__ void rr_read_sums(const RrSeg& s, const double (*tot)[2],
-                                             double* sum) {
-  double2 t[kRrWaves];
-#pragma unroll
-  for (int w = 0; w < kRrWaves; ++w) t[w] = *reinterpret_cast<const double2*>(tot[w]);
-  double v0 = t[0].x, v1 = t[0].y;
-#pragma unroll
-  for (int w = 1; w < kRrWaves; ++w) {
-    const double a0 = v0 + t[w].x, a1 = v1 + t[w].y;
-    v0 = w < s.nw ? a0 : v0;
-    v1 = w < s.nw ? a1 : v1;
-  }
-  sum[0] = uniform(v0);
-  if (D > 1) sum[1] = uniform(v1);
-}
-
-struct RrId {
-  __device__ double operator()(double a, double) const { return a; }
-};
-
-// Classic direction update p = r + beta p_old (p = r on the first iteration).
-struct RrDir {
-  double be;
-  bool first;
-  __device__ double operator()(double rv, double pv) const {
-    return first ? rv : fma(be, pv, rv);
-  }
-};
-
-// true residual b - A x of the final iterate: slot (t,t); res2 = its sum
-__device__ __forceinline__ void rr_final_residual(const PassArgs& a, const RrSeg& s, State& st,
-                                                  const RrVec& x, RrXchg& X,
-                                                  double (*tot_out)[2]) {
-  rr_publish(x, s, X);
-  __syncthreads();
-  RrVec b;
-  rr_load(a.b, s, b);
-  const auto h = rr_halo(s, X, nullptr, RrId());
-  double acc[1] = {0.0};
-#pragma unroll
-  for (int e = 0; e < kRrRows; ++e) {
-    const double t = b[e] - rr_st5(x, e > 0 ? x[e - 1] : 0.0, s, h, e);
-    acc[0] = fma(t, t, acc[0]);
-  }
-  rr_publish_sums<1>(acc, s, tot_out);
-  __syncthreads();
-  double sum[1];
-  rr_read_sums<1>(s, tot_out, sum);
-  st.res2 = sum[0];
-}
-
-// One pass of Algorithm 2's loop (the K_PCG pass): sums of the previous
-// pass, transition, then nvec = A w and the z, q, p, x, r, w recurrences with
-// slots (r,r), (w,r).  FIRST: the first loop pass (z = nvec, q = w, p = r).
-// Returns false when the solve stops.
-template <bool FIRST>
-__device__ __forceinline__ bool rr_pcg_pass(const RrSeg& s, RrLdsPcg& L, int& par, State& st,
-                                            RrVec& r, RrVec& w, RrVec& p, RrVec& q, RrVec& z) {
-  double sum[2];
-  Sc sc;
-  rr_read_sums<2>(s, L.tot[par], sum);
-  if (!transition<K_PCG>(st, sum, sc)) return false;
-  rr_uniform(st, sc);
-  const double al = sc.al, be = sc.be, nal = -sc.al;
-  const auto h = rr_halo(s, L.x[par], nullptr, RrId());
-  double ac[2] = {0.0, 0.0};
-  double wprev = 0.0;  // w[e-1] of this pass (w is updated in place)
-#pragma unroll
-  for (int e = 0; e < kRrRows; ++e) {
-    const double nv = rr_st5(w, wprev, s, h, e);
-    wprev = w[e];
-    if (FIRST) {
-      z[e] = nv;
-      q[e] = w[e];
-      p[e] = r[e];
-    } else {
-      z[e] = fma(be, z[e], nv);
-      q[e] = fma(be, q[e], w[e]);
-      p[e] = fma(be, p[e], r[e]);
-    }
-    L.xs[e][s.t] = fma(al, p[e], L.xs[e][s.t]);
-    r[e] = fma(nal, q[e], r[e]);
-    w[e] = fma(nal, z[e], w[e]);
-    ac[0] = fma(r[e], r[e], ac[0]);
-    ac[1] = fma(w[e], r[e], ac[1]);
-  }
-  par ^= 1;
-  rr_publish(w, s, L.x[par]);
-  rr_publish_sums<2>(ac, s, L.tot[par]);
-  __syncthreads();
-  return true;
-}
-
-// Pipelined CG (Algorithm 2) on one grid, x in LDS.
-__device__ __forceinline__ void rr_solve_pcg(const PassArgs& a, State& st, char* raw) {
-  RrLdsPcg& L = *reinterpret_cast<RrLdsPcg*>(raw);
-  const RrSeg s = rr_seg(a.g);
-  RrVec r, w, p, q, z;
-  Sc sc;
-  int par = 0;
-  double sum[2] = {0.0, 0.0};
-  rr_clear_edge0(L.x[0]);
-  rr_clear_edge0(L.x[1]);
-  {
-    RrVec x;
-    rr_load(a.x, s, x);
-#pragma unroll
-    for (int e = 0; e < kRrRows; ++e) L.xs[e][s.t] = x[e];
-    rr_publish(x, s, L.x[par]);
-    __syncthreads();
-    // r = b - A x; slots (r,r), (b,b)
-    transition<K_INIT_R>(st, sum, sc);
-    RrVec b;
-    rr_load(a.b, s, b);
-    const auto h = rr_halo(s, L.x[par], nullptr, RrId());
-    double acc[2] = {0.0, 0.0};
-#pragma unroll
-    for (int e = 0; e < kRrRows; ++e) {
-      r[e] = b[e] - rr_st5(x, e > 0 ? x[e - 1] : 0.0, s, h, e);
-      acc[0] = fma(r[e], r[e], acc[0]);
-      acc[1] = fma(b[e], b[e], acc[1]);
-    }
-    par ^= 1;
-    rr_publish(r, s, L.x[par]);
-    rr_publish_sums<2>(acc, s, L.tot[par]);
-    __syncthreads();
-  }
-  rr_read_sums<2>(s, L.tot[par], sum);
-  if (transition<K_INIT_W>(st, sum, sc)) {
-    // w = A r; slots (r,r), (w,r)
-    const auto h = rr_halo(s, L.x[par], nullptr, RrId());
-    double acc[2] = {0.0, 0.0};
-#pragma unroll
-    for (int e = 0; e < kRrRows; ++e) {
-      w[e] = rr_st5(r, e > 0 ? r[e - 1] : 0.0, s, h, e);
-      acc[0] = fma(r[e], r[e], acc[0]);
-      acc[1] = fma(w[e], r[e], acc[1]);
-    }
-    par ^= 1;
-    rr_publish(w, s, L.x[par]);
-    rr_publish_sums<2>(acc, s, L.tot[par]);
-    __syncthreads();
-    bool go = rr_pcg_pass<true>(s, L, par, st, r, w, p, q, z);
-    while (go) go = rr_pcg_pass<false>(s, L, par, st, r, w, p, q, z);
-  }
-  RrVec x;
-#pragma unroll
-  for (int e = 0; e < kRrRows; ++e) x[e] = L.xs[e][s.t];
-  if (st.status != ST_ZERO_RHS) {
-    par ^= 1;
-    rr_final_residual(a, s, st, x, L.x[par], L.tot[par ^ 1]);
-  }
-  rr_store(a.x, s, x);
-}
-
-// Algorithm 1, first pass of an iteration (the K_CG1 pass): beta; p = r +
-// beta p, also on the halo; s = A p; slot (p, s).  FIRST: p = r.
-template <bool FIRST>
-__device__ __forceinline__ bool rr_cg1_pass(const RrSeg& s, RrLdsCg& L, int& par, State& st,
-                                            const RrVec& r, RrVec& p, RrVec& sv) {
-  double sum[2];
-  Sc sc;
-  if (st.flags & F_BB_PENDING) rr_read_sums<2>(s, L.tot[par], sum);
-  else rr_read_sums<1>(s, L.tot[par], sum);
-  if (!transition<K_CG1>(st, sum, sc)) return false;
-  rr_uniform(st, sc);
-  const RrDir dir{sc.be, FIRST};
-  const auto h = rr_halo(s, L.x[par][0], &L.x[par][1], dir);
-  double acc[1] = {0.0};
-#pragma unroll
-  for (int e = 0; e < kRrRows; ++e) p[e] = dir(r[e], p[e]);
-#pragma unroll
-  for (int e = 0; e < kRrRows; ++e) {
-    sv[e] = rr_st5(p, e > 0 ? p[e - 1] : 0.0, s, h, e);
-    acc[0] = fma(p[e], sv[e], acc[0]);
-  }
-  par ^= 1;
-  rr_publish_sums<1>(acc, s, L.tot[par]);
-  __syncthreads();
-  return true;
-}
-
-// Algorithm 1, second pass (the K_CG2 pass): alpha; x += alpha p;
-// r -= alpha s; slot (r, r).
-__device__ __forceinline__ bool rr_cg2_pass(const RrSeg& s, RrLdsCg& L, int& par, State& st,
-                                            RrVec& x, RrVec& r, const RrVec& p,
-                                            const RrVec& sv) {
-  double sum[1];
-  Sc sc;
-  rr_read_sums<1>(s, L.tot[par], sum);
-  if (!transition<K_CG2>(st, sum, sc)) return false;
-  rr_uniform(st, sc);
-  const double al = sc.al, nal = -sc.al;
-  double acc[1] = {0.0};
-#pragma unroll
-  for (int e = 0; e < kRrRows; ++e) {
-    x[e] = fma(al, p[e], x[e]);
-    r[e] = fma(nal, sv[e], r[e]);
-    acc[0] = fma(r[e], r[e], acc[0]);
-  }
-  par ^= 1;
-  rr_publish(r, s, L.x[par][0]);
-  rr_publish(p, s, L.x[par][1]);
-  rr_publish_sums<1>(acc, s, L.tot[par]);
-  __syncthreads();
-  return true;
-}
-
-// Classic CG (Algorithm 1) on one grid, every vector in registers.
-__device__ __forceinline__ void rr_solve_cg(const PassArgs& a, State& st, char* raw) {
-  RrLdsCg& L = *reinterpret_cast<RrLdsCg*>(raw);
-  const RrSeg s = rr_seg(a.g);
-  RrVec x, r, p, sv;
-  Sc sc;
-  int par = 0;
-  double sum[2] = {0.0, 0.0};
-  rr_clear_edge0(L.x[0][0]);
-  rr_clear_edge0(L.x[0][1]);
-  rr_clear_edge0(L.x[1][0]);
-  rr_clear_edge0(L.x[1][1]);
-  rr_load(a.x, s, x);
-  rr_publish(x, s, L.x[par][0]);
-  __syncthreads();
-  {
-    // r = b - A x; slots (r,r), (b,b)
-    transition<K_INIT_R>(st, sum, sc);
-    RrVec b;
-    rr_load(a.b, s, b);
-    const auto h = rr_halo(s, L.x[par][0], nullptr, RrId());
-    double acc[2] = {0.0, 0.0};
-#pragma unroll
-    for (int e = 0; e < kRrRows; ++e) {
-      r[e] = b[e] - rr_st5(x, e > 0 ? x[e - 1] : 0.0, s, h, e);
-      acc[0] = fma(r[e], r[e], acc[0]);
-      acc[1] = fma(b[e], b[e], acc[1]);
-      p[e] = 0.0;
-    }
-    par ^= 1;
-    rr_publish(r, s, L.x[par][0]);
-    rr_publish(p, s, L.x[par][1]);
-    rr_publish_sums<2>(acc, s, L.tot[par]);
-    __syncthreads();
-  }
-  bool go = rr_cg1_pass<true>(s, L, par, st, r, p, sv) && rr_cg2_pass(s, L, par, st, x, r, p, sv);
-  while (go)
-    go = rr_cg1_pass<false>(s, L, par, st, r, p, sv) && rr_cg2_pass(s, L, par, st, x, r, p, sv);
-  if (st.status != ST_ZERO_RHS) {
-    par ^= 1;
-    rr_final_residual(a, s, st, x, L.x[par][0], L.tot[par ^ 1]);
-  }
-  rr_store(a.x, s, x);
-}
-
-template <int VARIANT>
-__global__ __launch_bounds__(kRrThreads) void k_solve_rr(PassArgs a) {
-  __shared__ __attribute__((aligned(16))) char raw[kRrLdsBytes];
-  State st = load_state_uniform(a.st_in);
-  if constexpr (VARIANT == 1) rr_solve_pcg(a, st, raw);
-  else rr_solve_cg(a, st, raw);
-  if (threadIdx.x == 0) *a.st_out = st;
-}
-
-// Many register-resident solves, one per work-group: work-group i solves the
-// resident solve in slot idx[i] (initial state in S[0]) and leaves its final
-// state, marked done for the step engine, in both S[0] and S[1].  A wider
-// work-group than the solve needs only adds idle wavefronts, whose zero sums
-// leave every dot product unchanged.
-__global__ __launch_bounds__(kRrThreads) void k_solve_rr_many(const Slot* slots,
-                                                              const int* idx) {
-  __shared__ __attribute__((aligned(16))) char raw[kRrLdsBytes];
-  const Slot& S = slots[__builtin_amdgcn_readfirstlane(idx[blockIdx.x])];
-  PassArgs a = {};
-  a.g = S.g;
-  a.b = S.b;
-  a.x = S.x;
-  State st = load_state_uniform(S.S[0]);
-  if (S.variant == 1) rr_solve_pcg(a, st, raw);
-  else rr_solve_cg(a, st, raw);
-  st.kind = K_DONE;
-  if (threadIdx.x == 0) {
-    *S.S[0] = st;
-    *S.S[1] = st;
-  }
-}
-
 // ---------------------------------------------------- multi-solve step --
 //
 // One launch advances every resident solve by one pass.  The work is a table
@@ -3081,21 +2613,6 @@ hipError_t launch_fill(void* p, size_t bytes, hipStream_t st) {
   if (n == 0) return hipSuccess;
   const int grid = (int)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
   hipLaunchKernelGGL(k_fill, dim3(grid), dim3(256), 0, st, (uint32_t*)p, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_solve_rr_many(const Slot* slots, const int* idx, int n, hipStream_t st) {
-  if (n < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_solve_rr_many, dim3(n), dim3(kRrThreads), 0, st, slots, idx);
-  return hipGetLastError();
-}
-
-hipError_t launch_solve_rr(int variant, const PassArgs& a, int threads, hipStream_t st) {
-  const int64_t need = (int64_t)(a.g.nx + 1) * ((a.g.ny + kRrRows - 1) / kRrRows);
-  if (threads < kWave || threads > kRrThreads || threads % kWave || need > threads)
-    return hipErrorInvalidValue;
-  if (variant == 1) hipLaunchKernelGGL((k_solve_rr<1>), dim3(1), dim3(threads), 0, st, a);
-  else hipLaunchKernelGGL((k_solve_rr<0>), dim3(1), dim3(threads), 0, st, a);
   return hipGetLastError();
 }
 

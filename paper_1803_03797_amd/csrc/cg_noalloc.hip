@@ -58,7 +58,7 @@ int scratch_of(int dev, void** out) {
 
 bool fits_on_chip(const cg_problem& p) {
   return p.precision == CG_PREC_FP64 && p.precond == 0 && p.nz <= 1 && !p.kx &&
-         (int64_t)(p.nx + 1) * ((p.ny + kRrRows - 1) / kRrRows) <= kRrThreads;
+         rr_rows(p.nx, p.ny) > 0;
 }
 
 }  // namespace

@@ -54,14 +54,6 @@ namespace {
 
 constexpr int kResWaves = kWavesPerTile;
 
-// A barrier that orders LDS only: global stores in flight (the exchange words)
-// are not waited for.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // The exchange area is addressed as global memory: through a pointer read from
 // memory the compiler would use flat accesses, which also occupy the LDS
 // counter.
@@ -105,10 +97,6 @@ __device__ __forceinline__ S load_uniform(const S* p) {
   S s;
   __builtin_memcpy(&s, u, sizeof(S));
   return s;
-}
-
-__device__ __forceinline__ bool uniform_flag(bool b) {
-  return __builtin_amdgcn_readfirstlane((int)b) != 0;
 }
 
 // Words of one value: 32 bits each.
@@ -232,41 +220,6 @@ __device__ __forceinline__ Around<T, CPL, NR> load_around(const T* V, const Geo&
       h.col[i] = V[(size_t)(p.j0 + i) * g.pitch + col];
   }
   return h;
-}
-
-// The butterfly of wave_sum (stage order 32, 16, ..., 1; addition commutes)
-// without LDS: xor 32 and 16 by gfx950's lane swaps, 8, 4, 2 and 1 by DPP.
-__device__ __forceinline__ double swap_add32(double v) {
-  const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
-  const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-  const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-}
-__device__ __forceinline__ double swap_add16(double v) {
-  const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
-  const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-  const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-}
-constexpr int kDppHalfMirror = 0x141;  // lane l of 8 gets lane l ^ 7
-constexpr int kDppXor3 = 0x1B;         // quad_perm [3,2,1,0]: lane l gets lane l ^ 3
-
-// A lane permutation that every lane takes part in.
-template <int CTRL>
-__device__ __forceinline__ double perm(double v) {
-  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
-  return __hiloint2double(hi, lo);
-}
-
-__device__ __forceinline__ double wave_sum_valu(double v) {
-  v = swap_add32(v);
-  v = swap_add16(v);
-  v = v + perm<kDppXor8>(v);
-  v = v + perm<kDppXor3>(perm<kDppHalfMirror>(v));  // l ^ 7 ^ 3 = l ^ 4
-  v = v + perm<kDppXor2>(v);
-  v = v + perm<kDppXor1>(v);
-  return v;
 }
 
 // What a thread reads and writes at every meeting: byte offsets within one
@@ -565,6 +518,14 @@ __device__ __forceinline__ void write_state(const ResSolve& a, const State& s, i
   *a.st_out = o;
 }
 
+template <typename T, int CPL>
+__device__ __forceinline__ Row<T, CPL> minus_zero() {
+  Row<T, CPL> v;
+#pragma unroll
+  for (int k = 0; k < CPL; ++k) v.e[k] = T(-0.0);
+  return v;
+}
+
 // The scalars of an iteration.  The loop forms them itself, with the
 // operations of transition<>, as long as nothing ends the solve; everything
 // else (the first iteration, a stop, a breakdown) goes through transition<>.
@@ -584,14 +545,6 @@ struct Scalars {
     return g > thr && g < __builtin_huge_val() && k < maxit;
   }
 };
-
-template <typename T, int CPL>
-__device__ __forceinline__ Row<T, CPL> minus_zero() {
-  Row<T, CPL> v;
-#pragma unroll
-  for (int k = 0; k < CPL; ++k) v.e[k] = T(-0.0);
-  return v;
-}
 
 // Row i of A v.
 template <typename T, int CPL>

@@ -19,7 +19,8 @@ struct Plan {
   int fp32g = 0;     // geometry of the FP32 lanes (4 columns per lane)
   bool wg = false;   // whole solve inside one work-group
   bool rr = false;   // ... with the vectors on chip (register-resident solver)
-  int rr_threads = 0;
+  int rr_threads = 0;  // ... its threads, and rows of a thread
+  int rr_rows = 0;
   bool fixed = false;  // fixed-point solve, one work-group (cg_fixed.hip)
   int precond = 0;     // Chebyshev preconditioner steps (classic FP64, tile passes)
   int cheb_rows = 0;   // ... rows of a Chebyshev item / partial tile

@@ -1404,9 +1404,22 @@ __global__ __launch_bounds__(kGroup) void k_final(PassArgs a) {
 // row J - (s - 1) of z is complete after step J.  West and east neighbours
 // come from the adjacent lanes (DPP); values near the wavefront's outer
 // columns lose one valid column per stage, so of the 128 columns the middle
-// 112 (the 8-column halo >= s - 1 on each side) are written.  Cells outside
-// the grid are held at zero through every stage (`MASK`, only for the
-// wavefronts and items that touch the grid edge).
+// 112 (the 8-column halo >= s - 1 on each side) are written.  Outside the grid
+// every level is zero: a wavefront at the west or east edge has its first or
+// last lane on the edge column and the lane shift fills in the zero (`MASK`
+// where that cannot be: the east edge of an odd or narrow grid); a stage runs
+// only on rows inside, and not before a row of it is needed.
+//
+// Bound by the FP64 pipeline (s = 8: 8 operations and a lane shift per cell and
+// stage at about 4.6 cycles a wavefront; 1.14 times the columns and 1.08 times
+// the rows are marched) and, while it was not prefetched far enough, by the wait
+// for r.  us a pass at 4096 x 4096, s = 8, classic / pipelined / binary32:
+//   94 / 97 / 56   r of row J - H read again from memory, every stage on all
+//                  H + H halo rows, masks on every edge item
+//   85 / 91 / 54   that r kept in LDS (the second load sat between the prefetch
+//                  and its wait), 4 c - w in one fma
+//   82 / 88 / 49   no idle halo stages, no masks
+//   76 / 83 / 49   7 rows loaded ahead instead of 2
 //
 // Items and partials.  A work-group of 8 wavefronts covers 8 x 112 = 896
 // columns, exactly 7 tiles of 128 columns, over the rows [ty H, (ty+1) H) of
@@ -1419,6 +1432,7 @@ constexpr int kChebHaloCols = 8;                                       // >= s -
 constexpr int kChebOut = 2 * kWave - 2 * kChebHaloCols;                // 112
 constexpr int kChebWaves = 8;
 constexpr int kChebThreads = kChebWaves * kWave;
+constexpr int kChebRingFrom = 7;
 constexpr int kChebGroupTiles = kChebWaves * kChebOut / (2 * kWave);   // 7
 static_assert(kChebGroupTiles * 2 * kWave == kChebWaves * kChebOut, "whole tiles per group");
 static_assert(kChebHaloCols >= kChebMaxSteps - 1, "halo too narrow for the steps");
@@ -1432,6 +1446,12 @@ struct V2 {
 };
 template <typename T>
 using Pair = std::conditional_t<sizeof(T) == 8, double2, float2>;
+
+// The rings of r of a work-group's wavefronts.
+template <int S, typename T>
+struct ChebRing {
+  Pair<T> row[kChebWaves][S >= kChebRingFrom ? S - 1 : 1][kWave];
+};
 
 constexpr int cgcd(int a, int b) { return b == 0 ? a : cgcd(b, a % b); }
 constexpr int clcm(int a, int b) { return a / cgcd(a, b) * b; }
@@ -1460,18 +1480,18 @@ template <int S, typename T>
 struct ChebRegs {
   static constexpr int H = S - 1;            // stencil steps = halo rows
   static constexpr int L = H > 0 ? H : 1;    // y / r ring length
-  static constexpr int PD = S <= 3 ? 4 : 2;  // rows loaded ahead
+  // rows loaded ahead (a divisor of P); binary32 of s = 8 fits two work-groups
+  // on a compute unit with 2 (49 us a pass), one with 7 (51 us)
+  static constexpr int PD = S <= 3 ? 4 : S == 8 && sizeof(T) == 4 ? 2 : L;
   static constexpr int P = clcm(clcm(2, L), PD);
-  // (r, z) needs r on row J-H at step J: kept in registers up to s = 6, read
-  // again (a cache hit: this wavefront read that row H steps before) one
-  // step ahead beyond, where the registers are needed for the stages
-  static constexpr bool RELOAD = S >= 7;
-  static constexpr int LR = RELOAD ? 1 : L;
+  // (r, z) needs r on row J-H at step J: kept in registers up to s = 6, in LDS
+  // (a ring of H rows per wavefront) beyond, where the registers are needed
+  static constexpr bool RING = S >= kChebRingFrom;
+  static constexpr int LR = RING ? 1 : L;
   V2<T> d[L][2];    // d_k on rows J-k-2, J-k-1 (slot (row - Jb) mod 2), levels k < H
   V2<T> rk[L][2];   // r_k on row J-k-1 (same slots)
   V2<T> y[L];       // y on rows J-H .. J-1 (slot (row - Jb) mod L)
-  V2<T> r0[LR];     // r on the same rows, for (r, z) (RELOAD: unused)
-  V2<T> rr[2];      // RELOAD: r on rows J-H, J-H+1 (slot (row - Jb) mod 2)
+  V2<T> r0[LR];     // r on the same rows, for (r, z) (RING: in LDS)
   V2<T> ld[PD];     // r loaded for rows J .. J+PD-1 (slot (row - Jb) mod PD)
   double a0, a1; // (r, z) column sums
 };
@@ -1480,39 +1500,55 @@ template <typename T>
 struct ChebCtx {
   const T* R;  // r + first column of the lane
   T* Z;        // z + first column of the lane
+  Pair<T>* ring;  // the lane's entry of the wavefront's LDS ring, row stride kWave
   int pitch, ny, y0, Je;
+  int Jb, sh;  // stage k runs from step Jb + (k << sh)
   bool v0, v1, outl;
 };
 
+// Row J of the input (zero past the grid; J >= 0).
 template <bool MASK, typename T>
 __device__ __forceinline__ V2<T> cheb_load(const ChebCtx<T>& c, int J) {
-  const int jl = min(max(J, 0), c.ny - 1);
+  const int jl = min(J, c.ny - 1);
   const Pair<T> t = *reinterpret_cast<const Pair<T>*>(c.R + (size_t)jl * c.pitch);
   V2<T> o;
   o.v[0] = t.x;
   o.v[1] = t.y;
   if constexpr (MASK) {
-    const bool rv = J >= 0 && J < c.ny;
-    o.v[0] = (rv && c.v0) ? o.v[0] : T(0);
-    o.v[1] = (rv && c.v1) ? o.v[1] : T(0);
+    o.v[0] = c.v0 ? o.v[0] : T(0);
+    o.v[1] = c.v1 ? o.v[1] : T(0);
   }
   return o;
 }
 
 // Step J = J0 + Q of the march; false once the item's rows are exhausted.
-template <int S, bool MASK, int Q, typename T>
+template <int S, bool MASK, bool ROWS, int Q, typename T>
 __device__ __forceinline__ bool cheb_step(const ChebCtx<T>& c, const T* c1, const T* c2, T c0,
                                           ChebRegs<S, T>& g, int J0) {
   using G = ChebRegs<S, T>;
   constexpr int H = G::H, L = G::L, PD = G::PD;
   const int J = J0 + Q;
   if (J >= c.Je) return false;
-  const V2<T> rin = g.ld[Q % PD];
+  V2<T> rin = g.ld[Q % PD];
   g.ld[Q % PD] = cheb_load<MASK>(c, J + PD);
+  if (ROWS && J >= c.ny) rin.v[0] = rin.v[1] = T(0);
   V2<T> rrow;
-  if constexpr (G::RELOAD) {
-    rrow = g.rr[cmod(Q - H, 2)];
-    g.rr[cmod(Q - H + 1, 2)] = cheb_load<MASK>(c, J - H + 1);
+  if constexpr (G::RING) {  // row J - H leaves its slot to row J
+    const Pair<T> t = c.ring[Q % L * kWave];
+    rrow.v[0] = t.x;
+    rrow.v[1] = t.y;
+    Pair<T> o;
+    o.x = rin.v[0];
+    o.y = rin.v[1];
+    c.ring[Q % L * kWave] = o;
+  }
+  // the stages that run, one bit each: those begun, on rows above ny (formed
+  // afresh each step, or the compiler keeps every stage's limits in registers)
+  int run = -1;
+  if constexpr (ROWS) {
+    run = (2 << min((J - c.Jb) >> c.sh, H)) - (1 << max(J - c.ny + 1, 0));
+    run = __builtin_amdgcn_readfirstlane(run);
+    asm volatile("" : "+s"(run));
   }
   // stage 0: d_0 = c0 r, y = d_0 on row J (zero outside the grid already)
   V2<T> dn, rn = rin, ynew;
@@ -1527,25 +1563,22 @@ __device__ __forceinline__ bool cheb_step(const ChebCtx<T>& c, const T* c1, cons
     // (slot sc) and J-k+1 (dn, this step)
     const int so = cmod(Q - (k - 1), 2), sc = so ^ 1;
     const V2<T> C = g.d[k - 1][sc], Sv = g.d[k - 1][so], Nv = dn;
-    const T w0 = dpp0<kDppWaveShr1>(C.v[1]);
-    const T e1 = dpp0<kDppWaveShl1>(C.v[0]);
-    const T W[2] = {w0, C.v[0]}, E[2] = {C.v[1], e1};
     V2<T> dk, rk;
+    dk.v[0] = dk.v[1] = rk.v[0] = rk.v[1] = T(0);
+    if (!ROWS || (run >> k & 1)) {
+      const T w0 = dpp0<kDppWaveShr1>(C.v[1]);
+      const T e1 = dpp0<kDppWaveShl1>(C.v[0]);
+      const T W[2] = {w0, C.v[0]}, E[2] = {C.v[1], e1};
+      V2<T>& yk = g.y[cmod(Q - k, L)];
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const T t = st5(C.v[e], W[e], E[e], Sv.v[e], Nv.v[e]);
-      rk.v[e] = g.rk[k - 1][sc].v[e] - t;
-      dk.v[e] = fma(c1[k - 1], C.v[e], c2[k - 1] * rk.v[e]);
+      for (int e = 0; e < 2; ++e) {
+        const T t = st5_fma(C.v[e], W[e], E[e], Sv.v[e], Nv.v[e]);
+        rk.v[e] = g.rk[k - 1][sc].v[e] - t;
+        dk.v[e] = fma(c1[k - 1], C.v[e], c2[k - 1] * rk.v[e]);
+        if constexpr (MASK) dk.v[e] = (e ? c.v1 : c.v0) ? dk.v[e] : T(0);
+        yk.v[e] = yk.v[e] + dk.v[e];
+      }
     }
-    if constexpr (MASK) {
-      const int j = J - k;
-      const bool rv = j >= 0 && j < c.ny;
-      dk.v[0] = (rv && c.v0) ? dk.v[0] : T(0);
-      dk.v[1] = (rv && c.v1) ? dk.v[1] : T(0);
-    }
-    V2<T>& yk = g.y[cmod(Q - k, L)];
-#pragma unroll
-    for (int e = 0; e < 2; ++e) yk.v[e] = yk.v[e] + dk.v[e];
     // level k-1's row J-k+1 replaces its row J-k-1 (used just now)
     g.d[k - 1][so] = dn;
     g.rk[k - 1][so] = rn;
@@ -1555,7 +1588,7 @@ __device__ __forceinline__ bool cheb_step(const ChebCtx<T>& c, const T* c1, cons
   // row J - H of z is complete (slot Q mod L, which row J takes next)
   constexpr int os = Q % L;
   const V2<T> zrow = H > 0 ? g.y[os] : ynew;
-  if constexpr (!G::RELOAD) rrow = H > 0 ? g.r0[os] : rin;
+  if constexpr (!G::RING) rrow = H > 0 ? g.r0[os] : rin;
   if (J >= c.y0 + H) {
     if (c.outl) {
       Pair<T> o;
@@ -1569,29 +1602,33 @@ __device__ __forceinline__ bool cheb_step(const ChebCtx<T>& c, const T* c1, cons
   }
   if constexpr (H > 0) {
     g.y[os] = ynew;
-    if constexpr (!G::RELOAD) g.r0[os] = rin;
+    if constexpr (!G::RING) g.r0[os] = rin;
   }
   return true;
 }
 
-template <int S, bool MASK, typename T, int... Qs>
+template <int S, bool MASK, bool ROWS, typename T, int... Qs>
 __device__ __forceinline__ bool cheb_period(const ChebCtx<T>& c, const T* c1, const T* c2, T c0,
                                             ChebRegs<S, T>& g, int J0,
                                             std::integer_sequence<int, Qs...>) {
-  return (cheb_step<S, MASK, Qs>(c, c1, c2, c0, g, J0) && ...);
+  return (cheb_step<S, MASK, ROWS, Qs>(c, c1, c2, c0, g, J0) && ...);
 }
 
 // R is the input vector, Z the output; ntx the 128-column tiles across the
 // padded row.  acc0/acc1 receive the (r, z) column sums of the lane's two
-// columns.
-template <int S, bool MASK, typename T>
-__device__ __forceinline__ void cheb_march(const PassArgs& a, const T* R, T* Z, int ntx, int cw,
-                                           int y0, int y1, double& acc0, double& acc1) {
+// columns.  ring: the wavefront's rows of r in LDS (S >= kChebRingFrom).
+// The lanes' columns start at bc.  MASK: columns outside the grid are kept at
+// zero; ROWS: stages run on the rows they are needed on, and rows outside the
+// grid are zero (else all rows y0 - H .. y1 + H are inside, and stages all run).
+template <int S, bool MASK, bool ROWS, typename T>
+__device__ __forceinline__ void cheb_march(const PassArgs& a, const T* R, T* Z, Pair<T>* ring,
+                                           int ntx, int cw, int bc, int y0, int y1, double& acc0,
+                                           double& acc1) {
   using G = ChebRegs<S, T>;
   constexpr int H = G::H, L = G::L, PD = G::PD, P = G::P;
   const Geo& gg = a.g;
   const int lane = threadIdx.x & (kWave - 1);
-  const int cl = cw - kChebHaloCols + 2 * lane;
+  const int cl = bc + 2 * lane;
   // the coefficients are uniform: scalar registers (binary32: each rounded
   // once from the binary64 coefficient)
   const T c0 = T(uniform(a.cheb[0]));
@@ -1613,11 +1650,12 @@ __device__ __forceinline__ void cheb_march(const PassArgs& a, const T* R, T* Z, 
   }
   c.R = R + lc;
   c.Z = Z + cl;
+  c.ring = ring + lane;
   c.pitch = gg.pitch;
   c.ny = gg.ny;
   c.y0 = y0;
   c.Je = y1 + H;
-  c.outl = lane >= kChebHaloCols / 2 && lane < kWave - kChebHaloCols / 2 && (!MASK || cl < gg.nx);
+  c.outl = cl >= cw && cl < min(cw + kChebOut, gg.nx);
   G g;
 #pragma unroll
   for (int k = 0; k < L; ++k)
@@ -1628,13 +1666,16 @@ __device__ __forceinline__ void cheb_march(const PassArgs& a, const T* R, T* Z, 
     }
 #pragma unroll
   for (int k = 0; k < G::LR; ++k) g.r0[k].v[0] = g.r0[k].v[1] = T(0);
-  g.rr[0] = g.rr[1] = g.r0[0];
   g.a0 = g.a1 = 0.0;
-  const int Jb = y0 - H;
+  // Rows from y0 - H; level k is good, and needed, from row y0 - (H - k) down,
+  // which is step 2 k.  From the top of the grid: from row 0, step k.
+  const int Jb = max(y0 - H, 0);
+  c.Jb = Jb;
+  c.sh = y0 > H ? 1 : 0;
 #pragma unroll
   for (int i = 0; i < PD; ++i) g.ld[i] = cheb_load<MASK>(c, Jb + i);
   for (int J0 = Jb; J0 < c.Je; J0 += P)
-    if (!cheb_period<S, MASK>(c, c1, c2, c0, g, J0, std::make_integer_sequence<int, P>{})) break;
+    if (!cheb_period<S, MASK, ROWS>(c, c1, c2, c0, g, J0, std::make_integer_sequence<int, P>{})) break;
   acc0 = g.a0;
   acc1 = g.a1;
 }
@@ -1652,7 +1693,8 @@ __device__ __forceinline__ int cheb_ntx(const Geo& g) {
 // `colacc` holds kChebWaves * kChebOut doubles.  FP64: a.r -> a.z; FP32 (the
 // refinement's inner solve): a.rf -> a.zf.
 template <int S, bool PIPE, typename T = double>
-__device__ __forceinline__ void cheb_item(const PassArgs& a, int it, int ngx, double* colacc) {
+__device__ __forceinline__ void cheb_item(const PassArgs& a, int it, int ngx, double* colacc,
+                                          ChebRing<S, T>& ring) {
   const Geo& g = a.g;
   const int ntx = cheb_ntx<T>(g);
   const T* R;
@@ -1670,20 +1712,35 @@ __device__ __forceinline__ void cheb_item(const PassArgs& a, int it, int ngx, do
   const int cw = gx * (kChebGroupTiles * 2 * kWave) + wave * kChebOut;
   const int y0 = ty * Hc, y1 = min(y0 + Hc, g.ny);
   double acc0 = 0.0, acc1 = 0.0;
+  int bc = cw == 0 ? 0 : cw - kChebHaloCols;  // first column of lane 0
   if (cw < g.nx) {
-    const bool inner = cw >= kChebHaloCols && cw + kChebOut + kChebHaloCols <= g.nx &&
-                       y0 >= S - 1 && y1 + (S - 1) <= g.ny;
-    if (inner) cheb_march<S, false>(a, R, Z, ntx, cw, y0, y1, acc0, acc1);
-    else cheb_march<S, true>(a, R, Z, ntx, cw, y0, y1, acc0, acc1);
+    // A wavefront at the grid's west or east edge starts (ends) its columns
+    // there: the lane shift then brings in the zero outside, and its steps need
+    // no masks.  Masks are left for the east edge of an odd or narrow grid.
+    if (bc + 2 * kWave > g.nx && g.nx >= 2 * kWave && (g.nx & 1) == 0) bc = g.nx - 2 * kWave;
+    Pair<T>* rg = ring.row[wave][0];
+    if (bc + 2 * kWave > g.nx)
+      cheb_march<S, true, true>(a, R, Z, rg, ntx, cw, bc, y0, y1, acc0, acc1);
+    else if (S <= 4 && y0 >= S - 1 && y1 + (S - 1) <= g.ny)
+      // few stages: running them all costs less than the choice (1024 x 1024,
+      // s = 4, us per iteration of classic CG: 30.8 and 31.2)
+      cheb_march<S, false, S >= 5>(a, R, Z, rg, ntx, cw, bc, y0, y1, acc0, acc1);
+    else
+      cheb_march<S, false, true>(a, R, Z, rg, ntx, cw, bc, y0, y1, acc0, acc1);
   }
   // PIPE: no partials, the fused pass sums its dots.  The column sums are
   // still formed: without them the compiler schedules the march of s = 8
   // into more than 256 registers and spills.
   if constexpr (PIPE) __asm__ volatile("" ::"v"(acc0), "v"(acc1));
-  if (!PIPE && lane >= kChebHaloCols / 2 && lane < kWave - kChebHaloCols / 2) {
-    double* c = colacc + wave * kChebOut + 2 * (lane - kChebHaloCols / 2);
-    c[0] = acc0;
-    c[1] = acc1;
+  if (!PIPE) {
+    // column sums of the lanes that hold output columns; zero beyond the grid
+    const int k = bc - cw + 2 * lane;
+    double* c = colacc + wave * kChebOut;
+    if (k >= 0 && k < kChebOut) {
+      c[k] = acc0;
+      c[k + 1] = acc1;
+    }
+    for (int z = 2 * kWave + bc - cw + lane; z < kChebOut; z += kWave) c[z] = 0.0;
   }
   __syncthreads();
   if (!PIPE && wave < kChebGroupTiles) {
@@ -1704,6 +1761,7 @@ __device__ __forceinline__ void cheb_item(const PassArgs& a, int it, int ngx, do
 template <int S, bool PIPE>
 __global__ __launch_bounds__(kChebThreads) void k_cheb(PassArgs a) {
   __shared__ double colacc[kChebWaves * kChebOut];
+  __shared__ ChebRing<S, double> ring;
   __shared__ double red[4 * 3];
   {
     State s = load_state_uniform(a.st_in);
@@ -1741,7 +1799,7 @@ __global__ __launch_bounds__(kChebThreads) void k_cheb(PassArgs a) {
   const int G = gridDim.x, b = blockIdx.x;
   const int xcd = b & 7, slot = b >> 3, nb = G >> 3;
   const int i0 = (int)(((int64_t)I * xcd) >> 3), i1 = (int)(((int64_t)I * (xcd + 1)) >> 3);
-  for (int it = i0 + slot; it < i1; it += nb) cheb_item<S, PIPE>(a, it, ngx, colacc);
+  for (int it = i0 + slot; it < i1; it += nb) cheb_item<S, PIPE>(a, it, ngx, colacc, ring);
 }
 
 // K_CHEBF: z = M^-1 r of the refinement's preconditioned inner solve, in
@@ -1752,6 +1810,7 @@ __global__ __launch_bounds__(kChebThreads) void k_cheb(PassArgs a) {
 template <int S>
 __global__ __launch_bounds__(kChebThreads) void k_chebf(PassArgs a) {
   __shared__ double colacc[kChebWaves * kChebOut];
+  __shared__ ChebRing<S, float> ring;
   __shared__ double red[4];
   {
     State s = load_state_uniform(a.st_in);
@@ -1781,7 +1840,7 @@ __global__ __launch_bounds__(kChebThreads) void k_chebf(PassArgs a) {
   const int G = gridDim.x, b = blockIdx.x;
   const int xcd = b & 7, slot = b >> 3, nb = G >> 3;
   const int i0 = (int)(((int64_t)I * xcd) >> 3), i1 = (int)(((int64_t)I * (xcd + 1)) >> 3);
-  for (int it = i0 + slot; it < i1; it += nb) cheb_item<S, false, float>(a, it, ngx, colacc);
+  for (int it = i0 + slot; it < i1; it += nb) cheb_item<S, false, float>(a, it, ngx, colacc, ring);
 }
 
 __global__ void k_fill(uint32_t* p, size_t n) {
@@ -2233,6 +2292,7 @@ __global__ __launch_bounds__(kChebThreads) void k_step_cheb(const Slot* slots, c
                                                            const int* cinfo,
                                                            const int* step_base, int k) {
   __shared__ double colacc[kChebWaves * kChebOut];
+  __shared__ ChebRing<S, std::conditional_t<F32, float, double>> ring;
   __shared__ double red[4 * 3];
   // this s's items: cinfo[2 s] items from items + cinfo[2 s + 1]
   const int n = __builtin_amdgcn_readfirstlane(cinfo[2 * S]);
@@ -2292,12 +2352,12 @@ __global__ __launch_bounds__(kChebThreads) void k_step_cheb(const Slot* slots, c
     }
     if constexpr (F32) {
       const int ngx = (cheb_ntx<float>(Sl.g) + kChebGroupTiles - 1) / kChebGroupTiles;
-      for (int ci = it.t0; ci < it.t1; ++ci) cheb_item<S, false, float>(a, ci, ngx, colacc);
+      for (int ci = it.t0; ci < it.t1; ++ci) cheb_item<S, false, float>(a, ci, ngx, colacc, ring);
     } else {
       const int ngx = (Sl.g.ntx + kChebGroupTiles - 1) / kChebGroupTiles;
       for (int ci = it.t0; ci < it.t1; ++ci) {
-        if (pipe) cheb_item<S, true>(a, ci, ngx, colacc);
-        else cheb_item<S, false>(a, ci, ngx, colacc);
+        if (pipe) cheb_item<S, true>(a, ci, ngx, colacc, ring);
+        else cheb_item<S, false>(a, ci, ngx, colacc, ring);
       }
     }
   }

@@ -190,10 +190,10 @@ __device__ __forceinline__ double rr_st5(const double (&v)[ROWS], double vs, con
   const double so = e > 0 ? vs : h.S;
   const double no = e + 1 < ROWS ? v[e + 1] : h.N;
   if constexpr (SEL) {
-    const double a = st5(v[e], w, ea, so, no);
+    const double a = st5_fma(v[e], w, ea, so, no);
     return e < s.nv ? a : 0.0;
   }
-  return e < s.nv ? st5(v[e], w, ea, so, no) : 0.0;
+  return e < s.nv ? st5_fma(v[e], w, ea, so, no) : 0.0;
 }
 
 template <int D>

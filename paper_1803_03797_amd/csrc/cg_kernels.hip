@@ -1747,7 +1747,7 @@ __device__ __forceinline__ void cheb_item(const PassArgs& a, int it, int ngx, do
     const int tx = gx * kChebGroupTiles + wave;
     if (tx < ntx) {
       const double* c = colacc + wave * 2 * kWave + 2 * lane;
-      const double v = wave_sum(c[0] + c[1]);
+      const double v = wave_sum_valu(c[0] + c[1]);
       if (lane == 0) a.part_out[(size_t)ty * ntx + tx] = v;
     }
   }
@@ -1876,7 +1876,7 @@ __device__ __forceinline__ void wg_pass(const PassArgs& a, const Sc& sc, double*
       double* L = lds + par * kWavesPerTile * DO;
 #pragma unroll
       for (int d = 0; d < DO; ++d) {
-        const double v = wave_sum(lv[d]);
+        const double v = wave_sum_valu(lv[d]);
         if (lane == 0) L[wave * DO + d] = v;
       }
       __syncthreads();

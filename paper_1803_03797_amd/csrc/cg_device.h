@@ -196,50 +196,61 @@ __device__ __forceinline__ double uniform(double v) {
   return __hiloint2double(hi, lo);
 }
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v = v + __shfl_xor(v, m, kWave);
-  return v;
-}
-
 // DPP controls that are xor permutations inside 16-lane rows.
 constexpr int kDppXor8 = 0x128;  // row_ror:8: lane l of a 16-lane row gets lane l ^ 8
 constexpr int kDppXor2 = 0x4E;   // quad_perm [2,3,0,1]: lane l gets lane l ^ 2
 constexpr int kDppXor1 = 0xB1;   // quad_perm [1,0,3,2]: lane l gets lane l ^ 1
 
-// The butterfly of wave_sum (stage order 32, 16, ..., 1; addition commutes)
-// without LDS: xor 32 and 16 by gfx950's lane swaps, 8, 4, 2 and 1 by DPP.
-__device__ __forceinline__ double swap_add32(double v) {
-  const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
-  const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-  const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-}
-__device__ __forceinline__ double swap_add16(double v) {
-  const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
-  const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-  const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-}
 constexpr int kDppHalfMirror = 0x141;  // lane l of 8 gets lane l ^ 7
 constexpr int kDppXor3 = 0x1B;         // quad_perm [3,2,1,0]: lane l gets lane l ^ 3
 
-// A lane permutation that every lane takes part in.
-template <int CTRL>
-__device__ __forceinline__ double perm(double v) {
-  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
-  return __hiloint2double(hi, lo);
+// 64-bit values (double or int64_t) across lanes without LDS: gfx950's lane
+// swaps exchange halves of 32 and of 16 lanes, DPP permutes within 16.
+template <typename T>
+__device__ __forceinline__ T from_halves(unsigned hi, unsigned lo) {
+  return __builtin_bit_cast(T, ((uint64_t)hi << 32) | lo);
+}
+template <typename T>
+__device__ __forceinline__ T swap_add32(T v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const unsigned lo = (unsigned)b, hi = (unsigned)(b >> 32);
+  const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+  return from_halves<T>(h[0], l[0]) + from_halves<T>(h[1], l[1]);
+}
+template <typename T>
+__device__ __forceinline__ T swap_add16(T v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const unsigned lo = (unsigned)b, hi = (unsigned)(b >> 32);
+  const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  return from_halves<T>(h[0], l[0]) + from_halves<T>(h[1], l[1]);
 }
 
-__device__ __forceinline__ double wave_sum_valu(double v) {
-  v = swap_add32(v);
-  v = swap_add16(v);
+// A lane permutation that every lane takes part in.
+template <int CTRL, typename T>
+__device__ __forceinline__ T perm(T v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const int lo = __builtin_amdgcn_mov_dpp((int)(unsigned)b, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(unsigned)(b >> 32), CTRL, 0xf, 0xf, true);
+  return from_halves<T>((unsigned)hi, (unsigned)lo);
+}
+
+// The sum over 16 lanes: an xor butterfly, stages 8, 4, 2, 1.
+template <typename T>
+__device__ __forceinline__ T row_sum_valu(T v) {
   v = v + perm<kDppXor8>(v);
   v = v + perm<kDppXor3>(perm<kDppHalfMirror>(v));  // l ^ 7 ^ 3 = l ^ 4
   v = v + perm<kDppXor2>(v);
   v = v + perm<kDppXor1>(v);
   return v;
+}
+
+// The sum over the wavefront: stages 32, 16, ..., 1 (every lane adds its xor
+// partner's value; addition commutes).
+template <typename T>
+__device__ __forceinline__ T wave_sum_valu(T v) {
+  return row_sum_valu(swap_add16(swap_add32(v)));
 }
 
 __device__ __forceinline__ bool uniform_flag(bool b) {

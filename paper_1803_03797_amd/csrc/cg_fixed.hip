@@ -34,15 +34,25 @@
 // lives in registers, Algorithm 2's x (and q from E = 8) in global memory.
 // The scalars of a converging solve take update forms without 64-bit
 // products (fx_upd); a uniform branch falls back to the general form.  Scalars are summed
-// by a wave butterfly, one LDS slot per wave and a second butterfly over the
-// slots; each thread then computes the same quotients, so no broadcast is
+// by a wave butterfly (lane swaps and DPP), one LDS slot per wave and a second
+// butterfly over the slots; each thread then computes the same quotients, so no broadcast is
 // needed.  Barriers per iteration: classic 3 (direction published, (p, s)
 // summed, (r, r) summed), pipelined 2 (all stencil reads of w done, (r, r)
 // and (w, r) summed).
+//
+// Bound by instruction issue in one compute unit (large grids) and by the chain
+// of sums, barriers and exact quotients (small ones).  us per iteration,
+// Algorithm 1 / 2, with LDS shuffles, 128-bit remainders, 64-bit compares and a
+// branch on every unknown -> as it stands:
+//   16 x 16    4.8 / 5.2  -> 3.8 / 4.0
+//   50 x 50    6.7 / 8.6  -> 5.4 / 6.7
+//   100 x 100  11.6 / 18.6 -> 10.3 / 14.4
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
+#include <utility>
 
+#include "cg_device.h"
 #include "cg_internal.h"
 
 namespace cgk {
@@ -57,8 +67,13 @@ constexpr int kFxRedHalf = kFxWaves * 2 * 2;  // [wave][value < 2][h, m]
 constexpr int kFxRed = 2 * kFxRedHalf;          // by call parity
 static_assert(kFxRed == kFxSumWords, "sum slots as the host budgets them");
 
+// By the high word: within [-2^17, 2^17) as it is, else the limit's words.
 __device__ __forceinline__ int64_t fx_clamp(int64_t v) {
-  return v > kFxMax ? kFxMax : (v < kFxMin ? kFxMin : v);
+  static_assert(kFxMax >> 32 == 0x1ffff && kFxMin >> 32 == -0x20000, "limits of the high word");
+  const int32_t hi = (int32_t)(v >> 32);
+  const int32_t hc = min(max(hi, -0x20000), 0x1ffff);
+  const uint32_t lo = hc == hi ? (uint32_t)v : ~(uint32_t)(hi >> 31);
+  return (int64_t)(((uint64_t)(uint32_t)hc << 32) | lo);
 }
 
 // v = h 2^30 + l, 0 <= l < 2^30; |h| <= 2^19 for |v| <= 2^49
@@ -121,6 +136,16 @@ constexpr int fx_form() {
   return COMMON ? M : FX_GENERAL;
 }
 
+// f(0), f(1), ... f(E - 1), the index a constant: as a loop, the ten unknowns'
+// arrays of Algorithm 2 at 100 x 100 were spilled whole (444 registers, 18.4 us an
+// iteration instead of 14.4).
+template <int E, class F>
+__device__ __forceinline__ void fx_each(F&& f) {
+  [&]<int... I>(std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+  }(std::make_integer_sequence<int, E>{});
+}
+
 // Exact running sum of Q(u v): u v rounded = h 2^30 + m.
 struct FxAcc {
   int64_t h, m;
@@ -155,24 +180,18 @@ __device__ __forceinline__ int64_t fx_finish(FxAcc a) {
 
 // Q(n / d) for d > 0: floor(n 2^30 / d + 1/2), saturated.  An FP64 estimate
 // is within 1/4 of n 2^30 / d + 1/2 when that is below 2^50 in magnitude, so
-// the floor of the estimate is off by at most one; the exact 128-bit
-// remainder of (n 2^31 + d) / (2 d) corrects it.
+// the floor of the estimate is off by at most one; the exact remainder of
+// (n 2^31 + d) / (2 d) corrects it.  That remainder lies within two divisors
+// (below 2^51), so its low 64 bits are all of it.
 __device__ __forceinline__ int64_t fx_div(int64_t n, int64_t d) {
   const double e = ldexp((double)n, 30) / (double)d + 0.5;
   if (e >= 0x1p50) return kFxMax;
   if (e <= -0x1p50) return kFxMin;
   int64_t q = (int64_t)floor(e);
-  const __int128 num = (__int128)n * ((__int128)1 << 31) + d;
-  const __int128 den = (__int128)d * 2;
-  __int128 rem = num - (__int128)q * den;
-  for (int i = 0; i < 2 && rem < 0; ++i) {
-    --q;
-    rem += den;
-  }
-  for (int i = 0; i < 2 && rem >= den; ++i) {
-    ++q;
-    rem -= den;
-  }
+  const int64_t den = d * 2;
+  const int64_t rem = (int64_t)(((uint64_t)n << 31) + (uint64_t)d - (uint64_t)q * (uint64_t)den);
+  if (rem < 0) q -= 1;
+  else if (rem >= den) q += 1;
   return fx_clamp(q);
 }
 
@@ -217,11 +236,8 @@ __device__ __forceinline__ void fx_sum(FxAcc (&a)[NV], int64_t* red, int& par,
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
     fx_norm(a[v]);
-#pragma unroll
-    for (int m = kWave / 2; m >= 1; m >>= 1) {
-      a[v].h += __shfl_xor((long long)a[v].h, m, kWave);
-      a[v].m += __shfl_xor((long long)a[v].m, m, kWave);
-    }
+    a[v].h = wave_sum_valu(a[v].h);
+    a[v].m = wave_sum_valu(a[v].m);
   }
   static_assert(NV >= 1 && NV <= 2, "two sums at most");
   int64_t* buf = red + par * kFxRedHalf;
@@ -242,11 +258,8 @@ __device__ __forceinline__ void fx_sum(FxAcc (&a)[NV], int64_t* red, int& par,
       s.h = buf[(lane * NV + v) * 2];
       s.m = buf[(lane * NV + v) * 2 + 1];
     }
-#pragma unroll
-    for (int m = kFxWaves / 2; m >= 1; m >>= 1) {
-      s.h += __shfl_xor((long long)s.h, m, kWave);
-      s.m += __shfl_xor((long long)s.m, m, kWave);
-    }
+    s.h = row_sum_valu(s.h);
+    s.m = row_sum_valu(s.m);
     out[v] = fx_uniform(fx_finish(s));
   }
   par ^= 1;
@@ -272,7 +285,9 @@ __device__ void fx_publish(const FxArgs& a, int status, int it, int64_t gamma, i
 // both nx * ny entries, then the sum slots.  Registers hold r and x
 // (Algorithm 1) or z, q and r (Algorithm 2); Algorithm 2's x stays in global
 // memory (xq), read and written once per iteration by its owner.
-template <int VARIANT, int E>
+// OWN: unknowns every thread is known to own (no branch on those: the loads of
+// several run together).
+template <int VARIANT, int E, int OWN>
 __device__ __forceinline__ void fx_solve(const FxArgs& a, int64_t* lds) {
   // Algorithm 2 with 8 or more unknowns per thread keeps q in global memory
   // too (qg): three register vectors of that many unknowns spill (measured:
@@ -291,11 +306,11 @@ __device__ __forceinline__ void fx_solve(const FxArgs& a, int64_t* lds) {
   const int maxit = a.S[0]->maxit;
 
   int c[E];  // -1: unowned
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
+  fx_each<E>([&](auto ie) {
+    constexpr int e = ie();
     const int k = t + e * T;
     c[e] = k < n ? k + k / nx + W : -1;
-  }
+  });
   for (int q = t; q < L; q += T) O[q] = 0;
   __syncthreads();
 
@@ -303,8 +318,8 @@ __device__ __forceinline__ void fx_solve(const FxArgs& a, int64_t* lds) {
   // and is read back by its owner (no register copy to hold meanwhile).
   int64_t xv[E];
   FxAcc acc[2] = {{0, 0}, {0, 0}};
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
+  fx_each<E>([&](auto ie) {
+    constexpr int e = ie();
     xv[e] = 0;
     if (c[e] >= 0) {
       const int k = t + e * T, j = c[e] - k - W, gk = j * pitch + (k - j * nx);
@@ -319,18 +334,18 @@ __device__ __forceinline__ void fx_solve(const FxArgs& a, int64_t* lds) {
       O[c[e]] = xv[e];
       fx_acc_sq(acc[0], bv);
     }
-  }
+  });
   __syncthreads();
   int64_t r[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
+  fx_each<E>([&](auto ie) {
+    constexpr int e = ie();
     r[e] = 0;
     if (c[e] >= 0) {
       const int k = t + e * T;
       r[e] = fx_clamp(a.bq[k] - fx_stencil(O, c[e], W));
       fx_acc_sq(acc[1], r[e]);
     }
-  }
+  });
   int64_t s2[2];
   fx_sum<2>(acc, red, par, s2);
   const int64_t bb = s2[0];
@@ -358,25 +373,25 @@ __device__ __forceinline__ void fx_solve(const FxArgs& a, int64_t* lds) {
       const FxSplit sb = fx_split(beta);
       fx_with(sb.h == 0, [&](auto common) {
         constexpr int MB = fx_form<common(), FX_ZERO>();
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-          if (c[e] >= 0) {
+        fx_each<E>([&](auto ie) {
+          constexpr int e = ie();
+          if (e < OWN || c[e] >= 0) {
             const int ce = fx_opaque(c[e]);
             O[ce] = it == 0 ? r[e] : fx_upd<MB>(sb, O[ce], r[e]);
           }
-        }
+        });
       });
       __syncthreads();
       FxAcc api[1] = {{0, 0}};
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        if (c[e] >= 0) {
+      fx_each<E>([&](auto ie) {
+        constexpr int e = ie();
+        if (e < OWN || c[e] >= 0) {
           const int k = fx_opaque(t) + e * T, ce = fx_opaque(c[e]);
           const int64_t sv = fx_stencil(O, ce, W);
           V[k] = sv;
           fx_acc(api[0], O[ce], sv);
         }
-      }
+      });
       int64_t pi[1];
       fx_sum<1>(api, red, par, pi);
       if (pi[0] <= 0) {
@@ -388,15 +403,15 @@ __device__ __forceinline__ void fx_solve(const FxArgs& a, int64_t* lds) {
       FxAcc ag[1] = {{0, 0}};
       fx_with(sa.h == 0 && sna.h == -1, [&](auto common) {
         constexpr int MA = fx_form<common(), FX_ZERO>(), MNA = fx_form<common(), FX_NEG>();
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-          if (c[e] >= 0) {
+        fx_each<E>([&](auto ie) {
+          constexpr int e = ie();
+          if (e < OWN || c[e] >= 0) {
             const int k = fx_opaque(t) + e * T, ce = fx_opaque(c[e]);
             xv[e] = fx_upd<MA>(sa, O[ce], xv[e]);
             r[e] = fx_upd<MNA>(sna, V[k], r[e]);
             fx_acc_sq(ag[0], r[e]);
           }
-        }
+        });
       });
       int64_t g2[1];
       fx_sum<1>(ag, red, par, g2);
@@ -406,36 +421,36 @@ __device__ __forceinline__ void fx_solve(const FxArgs& a, int64_t* lds) {
     }
   } else {
     // Algorithm 2: w = A r and delta = (w, r) first; then w in O, p in V
-#pragma unroll
-    for (int e = 0; e < E; ++e)
-      if (c[e] >= 0) O[c[e]] = r[e];
+    fx_each<E>([&](auto ie) {
+      constexpr int e = ie();
+      if (e < OWN || c[e] >= 0) O[c[e]] = r[e];
+    });
     __syncthreads();
     int64_t delta;
     {
       int64_t w0[E];
       FxAcc ad[1] = {{0, 0}};
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
+      fx_each<E>([&](auto ie) {
+        constexpr int e = ie();
         w0[e] = 0;
-        if (c[e] >= 0) {
+        if (e < OWN || c[e] >= 0) {
           w0[e] = fx_stencil(O, c[e], W);
           fx_acc(ad[0], w0[e], r[e]);
         }
-      }
+      });
       int64_t d1[1];
       fx_sum<1>(ad, red, par, d1);
       delta = d1[0];
-#pragma unroll
-      for (int e = 0; e < E; ++e)
-        if (c[e] >= 0) O[c[e]] = w0[e];
+      fx_each<E>([&](auto ie) {
+        constexpr int e = ie();
+        if (e < OWN || c[e] >= 0) O[c[e]] = w0[e];
+      });
     }
     __syncthreads();
     int64_t z[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) z[e] = 0;
+    fx_each<E>([&](auto ie) { z[ie()] = 0; });
     int64_t q[QG ? 1 : E];
-#pragma unroll
-    for (int e = 0; e < (QG ? 1 : E); ++e) q[e] = 0;
+    fx_each<(QG ? 1 : E)>([&](auto ie) { q[ie()] = 0; });
     int64_t alpha = 0, gamma_old = 0;
     for (;;) {
       if ((status = stop(gamma, it)) != ST_RUNNING) break;
@@ -464,10 +479,10 @@ __device__ __forceinline__ void fx_solve(const FxArgs& a, int64_t* lds) {
       // n = A w and z = n + beta z (first iteration: beta = 0, z = q = p = 0)
       fx_with(common, [&](auto cm) {
         constexpr int MB = fx_form<cm(), FX_ZERO>();
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-          if (c[e] >= 0) z[e] = fx_upd<MB>(sb, z[e], fx_stencil(O, fx_opaque(c[e]), W));
-        }
+        fx_each<E>([&](auto ie) {
+          constexpr int e = ie();
+          if (e < OWN || c[e] >= 0) z[e] = fx_upd<MB>(sb, z[e], fx_stencil(O, fx_opaque(c[e]), W));
+        });
       });
       __syncthreads();  // w is overwritten below
       FxAcc gd[2] = {{0, 0}, {0, 0}};
@@ -477,20 +492,20 @@ __device__ __forceinline__ void fx_solve(const FxArgs& a, int64_t* lds) {
         // x (and q) of the next unknown are loaded before this one's stores:
         // the global latency overlaps a whole unknown's arithmetic
         int64_t xn = 0, qn = 0;
-        if (c[0] >= 0) {
+        if (0 < OWN || c[0] >= 0) {
           const int k0 = fx_opaque(t);
           xn = a.xq[k0];
           if constexpr (QG) qn = a.qg[k0];
         }
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
+        fx_each<E>([&](auto ie) {
+          constexpr int e = ie();
           const int64_t xc = xn, qc = qn;
-          if (e + 1 < E && c[e + 1 < E ? e + 1 : e] >= 0) {
+          if (e + 1 < OWN || (e + 1 < E && c[e + 1 < E ? e + 1 : e] >= 0)) {
             const int kn = fx_opaque(t) + (e + 1) * T;
             xn = a.xq[kn];
             if constexpr (QG) qn = a.qg[kn];
           }
-          if (c[e] >= 0) {
+          if (e < OWN || c[e] >= 0) {
             const int k = fx_opaque(t) + e * T, ce = fx_opaque(c[e]);
             const int64_t w = O[ce];
             int64_t qe;
@@ -509,7 +524,7 @@ __device__ __forceinline__ void fx_solve(const FxArgs& a, int64_t* lds) {
             fx_acc_sq(gd[0], r[e]);
             fx_acc(gd[1], wn, r[e]);
           }
-        }
+        });
       });
       int64_t sums[2];
       fx_sum<2>(gd, red, par, sums);
@@ -518,27 +533,29 @@ __device__ __forceinline__ void fx_solve(const FxArgs& a, int64_t* lds) {
       delta = sums[1];
       ++it;
     }
-#pragma unroll
-    for (int e = 0; e < E; ++e)
-      if (c[e] >= 0) xv[e] = a.xq[t + e * T];
+    fx_each<E>([&](auto ie) {
+      constexpr int e = ie();
+      if (e < OWN || c[e] >= 0) xv[e] = a.xq[t + e * T];
+    });
   }
 
   // true residual b - A x in the same arithmetic, then x back to FP64
   __syncthreads();
-#pragma unroll
-  for (int e = 0; e < E; ++e)
+  fx_each<E>([&](auto ie) {
+    constexpr int e = ie();
     if (c[e] >= 0) O[c[e]] = xv[e];
+  });
   __syncthreads();
   FxAcc at[1] = {{0, 0}};
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
+  fx_each<E>([&](auto ie) {
+    constexpr int e = ie();
     if (c[e] >= 0) {
       const int k = t + e * T, j = c[e] - k - W;
       const int64_t tv = fx_clamp(a.bq[k] - fx_stencil(O, c[e], W));
       fx_acc_sq(at[0], tv);
       a.x[j * pitch + (k - j * nx)] = ldexp((double)xv[e], -30);
     }
-  }
+  });
   int64_t tt[1];
   fx_sum<1>(at, red, par, tt);
   if (t == 0) fx_publish(a, status, it, gamma, bb, tt[0]);
@@ -547,7 +564,10 @@ __device__ __forceinline__ void fx_solve(const FxArgs& a, int64_t* lds) {
 template <int VARIANT, int E>
 __global__ __launch_bounds__(kFxThreads) void k_solve_fixed(FxArgs a) {
   __shared__ int64_t lds[kFxLdsWords];
-  fx_solve<VARIANT, E>(a, lds);
+  // The launch takes the smallest E that covers the grid.  From 8 unknowns
+  // (Algorithm 2) or 10 the loads run together spill.
+  constexpr int OWN = E == 10 || (VARIANT == 1 && E == 8) ? 0 : fixed_elems_below(E);
+  fx_solve<VARIANT, E, OWN>(a, lds);
 }
 
 // One work-group per listed slot; every listed slot runs VARIANT and has at
@@ -566,7 +586,7 @@ __global__ __launch_bounds__(kFxThreads) void k_solve_fixed_many(const Slot* slo
   a.qg = reinterpret_cast<int64_t*>(S.q);
   a.S[0] = S.S[0];
   a.S[1] = S.S[1];
-  fx_solve<VARIANT, E>(a, lds);
+  fx_solve<VARIANT, E, 0>(a, lds);
 }
 
 template <int VARIANT>

@@ -286,6 +286,8 @@ inline int fixed_elems(int64_t dof, int threads) {
   const int64_t e = (dof + threads - 1) / threads;
   return e <= 4 ? (int)(e < 1 ? 1 : e) : e <= 6 ? 6 : e <= 8 ? 8 : 10;
 }
+// The unknowns every thread then owns: more would be covered by fewer.
+constexpr int fixed_elems_below(int e) { return e <= 4 ? e - 1 : e - 2; }
 
 struct FxArgs {
   Geo g;

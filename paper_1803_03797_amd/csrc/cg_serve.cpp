@@ -308,6 +308,9 @@ class Engine {
     bool looping = false;
     int rc = launch_loop(looping);
     if (rc) return rc;
+    // solves that found no room in the arena for their launch take these steps:
+    // steps without their items would leave their state behind
+    if (dirty_ && upload_items()) return CG_E_DEVICE;
     if (step_jobs_) rc = run_steps(looping ? 4 : steps);
     return looping ? finish_loop(rc) : rc;
   }

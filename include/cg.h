@@ -225,7 +225,12 @@ typedef struct {
   size_t footprint;         /* device bytes the solve occupies                       */
 } cg_plan_info;
 
-/* Per-kernel timing gathered while profiling is on (cg_set_profiling). */
+/* Per-kernel timing gathered while profiling is on (cg_set_profiling).  Counted
+ * whether it is on or not, without time and bytes: the launches of mid-size
+ * solves' iteration loops, a solve each, as resident_<cg, pcg or cg_f32>_<rows>x
+ * <strips>_<near or far>, and resident_abandoned, the solves whose loop was given
+ * up because the device was not free for it (they ran by passes from the start,
+ * with the same result).  While profiling is on every solve runs by passes. */
 typedef struct {
   char name[32];
   int64_t launches;

@@ -901,6 +901,17 @@ ResSolve resident_solve(Work& w, const State* st, const double* part, int budget
   return a;
 }
 
+// The statistics count the launches of the loop by form, whether profiling is
+// on or not (nothing else tells a solve in the loop from one by passes, which
+// gives the same bits), and the solves that were abandoned.
+void count_resident(Ctx& c, int kind, int rows, int strips, bool near) {
+  static const char* const kinds[] = {"cg", "pcg", "cg_f32"};
+  char name[32];
+  snprintf(name, sizeof(name), "resident_%s_%dx%d_%s", kinds[kind], rows, strips,
+           near ? "near" : "far");
+  c.prof_add(name, 0.0, 0.0, 1);
+}
+
 constexpr int kAbandoned = 1;  // run_resident: the solve is to be run by passes
 
 // Runs a solve whose next pass begins an odd iteration (K_CG1, K_PCG, K_CG1F)
@@ -911,6 +922,7 @@ static int run_resident(Ctx& c, Work& w, const Resident& r, State& s) {
     const ResSolve a = resident_solve(w, w.S[w.m & 1], w.part[w.m & 1], c.resident_budget,
                                       c.resident_spin);
     HIPCHK(launch_resident(r.kind, w.pl.g.rows, r.strips, r.near, a, r.wgs, c.st));
+    count_resident(c, r.kind, w.pl.g.rows, r.strips, r.near);
     char* flag = c.host_state + 2048;  // pinned, past the state and the coefficients
     HIPCHK(hipMemcpyAsync(flag, w.sync, sizeof(uint64_t), hipMemcpyDeviceToHost, c.st));
     int rc = read_state(c, w, s);
@@ -1126,6 +1138,7 @@ int Ctx::solve(const cg_problem* p, cg_result* res) {
                   : solve_tiled(c, w, p, s, r);
   if (rc == kAbandoned && !w.pl.wg) {
     // the device was not free for all of the solve's work-groups at once
+    c.prof_add(kResidentAbandoned, 0.0, 0.0, 1);
     if ((rc = stage_in(c, w, p))) return rc;
     rc = solve_tiled(c, w, p, s, Resident());
   }

@@ -104,6 +104,10 @@ Resident resident_of(const Ctx& c, const Plan& pl);
 // The solve as it stands, for a launch of `budget` iterations; numbers its meetings.
 cgk::ResSolve resident_solve(Work& w, const cgk::State* st, const double* part, int budget,
                              int spin);
+// Counts a launch of the loop in the context's statistics; an abandoned solve
+// is counted under kResidentAbandoned.
+void count_resident(Ctx& c, int kind, int rows, int strips, bool near);
+constexpr const char* kResidentAbandoned = "resident_abandoned";
 // Held while resident launches are on the device: their work-groups wait for
 // each other, so two launches that both fit alone must not share it.
 std::mutex& resident_mutex(int device);

@@ -457,6 +457,7 @@ class Engine {
       hd[id] = resident_solve(j->w, j->w.S[j->parity], j->w.part[j->parity], kLoopBudget,
                               c_.resident_spin);
       hd[id].form = resident_form(j->kind, h, near);
+      count_resident(c_, j->kind, j->w.pl.g.rows, h, near);
       for (int g = 0; g < n; ++g) {
         if (!near) at = (int)(std::min_element(used.begin(), used.end()) - used.begin());
         cell(at) = ResWg{id, g};
@@ -546,6 +547,7 @@ class Engine {
 
   // A solve that its launch abandoned: from the start, by steps.
   int restart(Job* j) {
+    c_.prof_add(kResidentAbandoned, 0.0, 0.0, 1);
     j->kind = -1;
     j->mode = Job::kStep;
     ++step_jobs_;

@@ -838,9 +838,9 @@ static int chunk_iters(Ctx& c, const Work& w) {
 
 // ------------------------------------------------------- resident loop --
 
-std::mutex& resident_mutex(int device) {
-  static std::mutex m[64];
-  return m[device & 63];
+ResidentTurn& resident_turn_of(int device) {
+  static ResidentTurn t[64];
+  return t[device & 63];
 }
 
 // Whether the iteration loop of a solve runs resident, and in which form.
@@ -917,11 +917,12 @@ constexpr int kAbandoned = 1;  // run_resident: the solve is to be run by passes
 // Runs a solve whose next pass begins an odd iteration (K_CG1, K_PCG, K_CG1F)
 // until its state stops it.
 static int run_resident(Ctx& c, Work& w, const Resident& r, State& s) {
-  std::lock_guard<std::mutex> lk(resident_mutex(c.device));
   for (;;) {
     const ResSolve a = resident_solve(w, w.S[w.m & 1], w.part[w.m & 1], c.resident_budget,
                                       c.resident_spin);
-    HIPCHK(launch_resident(r.kind, w.pl.g.rows, r.strips, r.near, a, r.wgs, c.st));
+    HIPCHK(resident_turn(c.device, c.st, [&] {
+      return launch_resident(r.kind, w.pl.g.rows, r.strips, r.near, a, r.wgs, c.st);
+    }));
     count_resident(c, r.kind, w.pl.g.rows, r.strips, r.near);
     char* flag = c.host_state + 2048;  // pinned, past the state and the coefficients
     HIPCHK(hipMemcpyAsync(flag, w.sync, sizeof(uint64_t), hipMemcpyDeviceToHost, c.st));

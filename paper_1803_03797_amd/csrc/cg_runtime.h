@@ -98,6 +98,15 @@ struct Resident {
   bool near = false;  // all work-groups on one XCD
 };
 
+// The resident launch issued last on a device, and its stream (a context waits
+// for its streams before it destroys them).
+struct ResidentTurn {
+  std::mutex m;
+  hipEvent_t done = nullptr;
+  hipStream_t last = nullptr;
+};
+ResidentTurn& resident_turn_of(int device);
+
 struct Ctx;
 double now_s();
 Resident resident_of(const Ctx& c, const Plan& pl);
@@ -108,9 +117,25 @@ cgk::ResSolve resident_solve(Work& w, const cgk::State* st, const double* part, 
 // is counted under kResidentAbandoned.
 void count_resident(Ctx& c, int kind, int rows, int strips, bool near);
 constexpr const char* kResidentAbandoned = "resident_abandoned";
-// Held while resident launches are on the device: their work-groups wait for
-// each other, so two launches that both fit alone must not share it.
-std::mutex& resident_mutex(int device);
+// Issues a resident launch (`launch`, on `st`) in its turn on the device: the
+// work-groups of a launch wait for each other, so two that both fit alone must
+// not share it.  The device itself waits for the launch before, one event a
+// device, and no lock is held meanwhile: launches of all contexts follow each
+// other in the order they were issued, each of a bounded number of iterations.
+template <class F>
+hipError_t resident_turn(int device, hipStream_t st, F launch) {
+  ResidentTurn& t = resident_turn_of(device);
+  std::lock_guard<std::mutex> lk(t.m);
+  hipError_t e = hipSuccess;
+  if (!t.done) e = hipEventCreateWithFlags(&t.done, hipEventDisableTiming);
+  else if (t.last != st) e = hipStreamWaitEvent(st, t.done, 0);
+  if (e != hipSuccess) return e;
+  t.last = st;
+  e = launch();
+  if (e == hipSuccess) e = hipEventRecord(t.done, st);
+  if (e != hipSuccess) (void)hipStreamSynchronize(st);
+  return e;
+}
 bool carve(Ctx& c, Work& w);
 int stage_in(Ctx& c, Work& w, const cg_problem* p);
 cgk::State initial_state(const cg_problem* p);

@@ -470,16 +470,18 @@ class Engine {
       return CG_OK;
     }
     // the solves' earlier passes are complete (their states have been read):
-    // nothing on the steps' stream, which may wait for a caller's, is waited
-    // for while the device is held
-    loop_lock_ = std::unique_lock<std::mutex>(resident_mutex(c_.device));
+    // the launch, and those of other contexts that follow it, wait for nothing
+    // on the steps' stream, which may wait for a caller's
     const int nr = (int)loop_run_.size();
     State* ds = (State*)(loop_mem_ + loop_desc_bytes() + loop_wgs_bytes());
     State* hs = (State*)(h_loop_ + loop_desc_bytes() + loop_wgs_bytes());
     if (hipMemcpyAsync(loop_mem_, h_loop_, loop_desc_bytes() + (size_t)grid * sizeof(ResWg),
                        hipMemcpyHostToDevice, c_.loop) ||
-        launch_resident_many((const ResSolve*)loop_mem_,
-                             (const ResWg*)(loop_mem_ + loop_desc_bytes()), grid, c_.loop) ||
+        resident_turn(c_.device, c_.loop, [&] {
+          return launch_resident_many((const ResSolve*)loop_mem_,
+                                      (const ResWg*)(loop_mem_ + loop_desc_bytes()), grid,
+                                      c_.loop);
+        }) ||
         launch_resident_states((const ResSolve*)loop_mem_, nr, ds, c_.loop) ||
         hipMemcpyAsync(hs, ds, (size_t)nr * sizeof(State), hipMemcpyDeviceToHost, c_.loop) ||
         hipEventRecord(loop_ev_, c_.loop)) {
@@ -494,7 +496,6 @@ class Engine {
   void drop_loop() {
     c_.arena.release(loop_mem_);
     loop_mem_ = nullptr;
-    if (loop_lock_.owns_lock()) loop_lock_.unlock();
   }
 
   // Waits for the loop's launch, with the other solves' steps beside it (a few
@@ -793,14 +794,13 @@ class Engine {
   hipEvent_t rr_ev_ = nullptr, stage_ev_ = nullptr;
   bool rr_pending_ = false;  // launched, not yet joined by a harvest
   // the resident loop: work-groups an XCD holds at once (0: no loop), and the
-  // launch in flight (its solves, tables, and the lock of the device)
+  // launch in flight (its solves and tables)
   static constexpr int kLoopBudget = 256;  // iterations a launch
   int loop_xcds_ = 8, loop_room_ = 0;
   hipEvent_t loop_ev_ = nullptr, step_ev_ = nullptr;
   char* loop_mem_ = nullptr;
   char* h_loop_ = nullptr;
   std::vector<Job*> loop_run_;
-  std::unique_lock<std::mutex> loop_lock_;
   int step_jobs_ = 0;        // resident solves that take step items
   int active_ = 0;
   int grid_ = 8;

@@ -14,15 +14,15 @@
 // chunk that follows their admission also launches them, one work-group
 // each, on a side stream, and the next harvest waits for them.  Mid-size
 // solves run their iterations in the resident loop (cg_resident.hip), many
-// solves to a launch beside the steps, and take step items only for the passes
-// before and after.
+// solves to a launch, and take step items only for the passes before and after.
+// Steps, harvests and admissions go on beside a launch in flight.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <chrono>
 #include <condition_variable>
 #include <cstring>
 #include <deque>
+#include <functional>
 #include <memory>
 #include <mutex>
 #include <thread>
@@ -64,8 +64,9 @@ class Engine {
   explicit Engine(Ctx& c, int nslots) : c_(c), n_(std::max(1, nslots)) {}
   ~Engine() {
     if (rr_pending_) (void)hipStreamSynchronize(c_.side);
+    if (loop_mem_) (void)hipStreamSynchronize(c_.loop);
+    drop_loop();
     if (loop_ev_) (void)hipEventDestroy(loop_ev_);
-    if (step_ev_) (void)hipEventDestroy(step_ev_);
     if (h_loop_) (void)hipHostFree(h_loop_);
     if (rr_ev_) (void)hipEventDestroy(rr_ev_);
     if (stage_ev_) (void)hipEventDestroy(stage_ev_);
@@ -130,7 +131,6 @@ class Engine {
       loop_room_ = resident_many_blocks_per_cu() >= 2 ? 2 * (c_.num_cu / loop_xcds_) : 0;
       const size_t host = loop_desc_bytes() + loop_wgs_bytes() + (size_t)n_ * sizeof(State);
       if (hipEventCreateWithFlags(&loop_ev_, hipEventDisableTiming) ||
-          hipEventCreateWithFlags(&step_ev_, hipEventDisableTiming) ||
           hipHostMalloc((void**)&h_loop_, host, hipHostMallocDefault))
         return CG_E_DEVICE;
     }
@@ -253,6 +253,11 @@ class Engine {
   // chunk when `steps` is the chunk length, plain launches otherwise.
   int run(int steps) {
     if (!active_) return CG_OK;
+    if (loop_mem_) {
+      const hipError_t e = hipEventQuery(loop_ev_);
+      if (e != hipErrorNotReady)
+        if (int rc = finish_loop(e)) return rc;
+    }
     if (dirty_ && upload_items()) return CG_E_DEVICE;
     if (!rr_new_.empty() || !fx_new_.empty()) {
       // newly admitted small and fixed-point solves: whole solves on the side
@@ -300,19 +305,24 @@ class Engine {
           c_.pending.push_back({f0, f1, "solve_fixed_many", 0.0});
         }
       }
+      // the register-resident solver fills a compute unit: where the loop holds
+      // them all its solves wait for the launch in flight.  The next ones are
+      // short, and become longer again while no more such solves arrive.
+      if (loop_mem_) loop_short_ = 3;
       if (hipEventRecord(rr_ev_, c_.side)) return CG_E_DEVICE;
       rr_new_.clear();
       fx_new_.clear();
       rr_pending_ = true;
     }
-    bool looping = false;
-    int rc = launch_loop(looping);
-    if (rc) return rc;
+    int rc = CG_OK;
+    if (!loop_mem_ && (rc = launch_loop())) return rc;
     // solves that found no room in the arena for their launch take these steps:
     // steps without their items would leave their state behind
     if (dirty_ && upload_items()) return CG_E_DEVICE;
-    if (step_jobs_) rc = run_steps(looping ? 4 : steps);
-    return looping ? finish_loop(rc) : rc;
+    // a launch in flight: few steps at a time, the next launch comes after them
+    if (step_jobs_) return run_steps(loop_mem_ ? 4 : steps);
+    if (loop_mem_ && !rr_pending_) return wait_loop();
+    return CG_OK;
   }
 
  private:
@@ -401,7 +411,7 @@ class Engine {
   // wait until the others leave room on every XCD).  Few strips per wavefront make an iteration short (300 x 190 classic
   // on one XCD 3.3 us with one or two, 3.6 with four), many let more solves in:
   // as many as it takes for all waiting solves to fit.
-  int launch_loop(bool& launched) {
+  int launch_loop() {
     loop_run_.clear();
     std::vector<Job*> wait;
     for (int i = 0; i < n_; ++i)
@@ -454,8 +464,8 @@ class Engine {
       }
       if (!h) continue;  // no room this time
       const int id = (int)loop_run_.size(), n = loop_wgs(j, h);
-      hd[id] = resident_solve(j->w, j->w.S[j->parity], j->w.part[j->parity], kLoopBudget,
-                              c_.resident_spin);
+      hd[id] = resident_solve(j->w, j->w.S[j->parity], j->w.part[j->parity],
+                              kLoopBudget >> loop_short_, c_.resident_spin);
       hd[id].form = resident_form(j->kind, h, near);
       count_resident(c_, j->kind, j->w.pl.g.rows, h, near);
       for (int g = 0; g < n; ++g) {
@@ -469,6 +479,7 @@ class Engine {
       drop_loop();
       return CG_OK;
     }
+    if (loop_short_) --loop_short_;
     // the solves' earlier passes are complete (their states have been read):
     // the launch, and those of other contexts that follow it, wait for nothing
     // on the steps' stream, which may wait for a caller's
@@ -489,31 +500,32 @@ class Engine {
       drop_loop();
       return CG_E_DEVICE;
     }
-    launched = true;
     return CG_OK;
   }
 
   void drop_loop() {
     c_.arena.release(loop_mem_);
     loop_mem_ = nullptr;
+    loop_run_.clear();
   }
 
-  // Waits for the loop's launch, with the other solves' steps beside it (a few
-  // at a time: the next launch waits for the last of them), and moves the
-  // solves that it has brought to a stop back to the steps.
-  int finish_loop(int rc) {
-    if (step_jobs_ && rc == CG_OK) {
-      if (hipEventRecord(step_ev_, c_.st)) rc = CG_E_DEVICE;
-      while (rc == CG_OK && hipEventQuery(loop_ev_) == hipErrorNotReady) {
-        if (hipEventQuery(step_ev_) == hipSuccess) {
-          rc = run_steps(2);
-          if (rc == CG_OK && hipEventRecord(step_ev_, c_.st)) rc = CG_E_DEVICE;
-        } else {
-          std::this_thread::sleep_for(std::chrono::microseconds(20));
-        }
-      }
+  // Nothing to do beside the launch in flight: waits for its end, or a
+  // newcomer, a millisecond at most (the context is the caller's meanwhile).
+  int wait_loop() {
+    for (const double t0 = now_s(); now_s() - t0 < 1e-3;) {
+      const hipError_t e = hipEventQuery(loop_ev_);
+      if (e == hipSuccess || (e == hipErrorNotReady && newcomers && newcomers())) return CG_OK;
+      if (e != hipErrorNotReady) return CG_E_DEVICE;
+      std::this_thread::yield();
     }
-    if (hipEventSynchronize(loop_ev_)) rc = CG_E_DEVICE;
+    return CG_OK;
+  }
+
+  // The launch has ended: moves the solves that it has brought to a stop back
+  // to the steps.
+  int finish_loop(hipError_t e) {
+    if (e != hipSuccess) return CG_E_DEVICE;
+    int rc = CG_OK;
     const State* hs = (const State*)(h_loop_ + loop_desc_bytes() + loop_wgs_bytes());
     for (size_t i = 0; i < loop_run_.size() && rc == CG_OK; ++i) {
       Job* j = loop_run_[i];
@@ -618,6 +630,8 @@ class Engine {
   void abandon(std::vector<Job*>& done, int rc) {
     if (rr_pending_) (void)hipStreamSynchronize(c_.side);
     rr_pending_ = false;
+    if (loop_mem_) (void)hipStreamSynchronize(c_.loop);
+    drop_loop();
     rr_new_.clear();
     fx_new_.clear();
     step_jobs_ = 0;
@@ -761,6 +775,7 @@ class Engine {
 
  public:
   bool this_is_serving_ = false;
+  std::function<bool()> newcomers;  // serving: a request waits to be admitted
 
  private:
   char* ctrl_ = nullptr;
@@ -796,9 +811,10 @@ class Engine {
   // the resident loop: work-groups an XCD holds at once (0: no loop), and the
   // launch in flight (its solves and tables)
   static constexpr int kLoopBudget = 256;  // iterations a launch
+  int loop_short_ = 0;  // halvings of the next launch's iterations
   int loop_xcds_ = 8, loop_room_ = 0;
-  hipEvent_t loop_ev_ = nullptr, step_ev_ = nullptr;
-  char* loop_mem_ = nullptr;
+  hipEvent_t loop_ev_ = nullptr;
+  char* loop_mem_ = nullptr;  // not null: in flight
   char* h_loop_ = nullptr;
   std::vector<Job*> loop_run_;
   int step_jobs_ = 0;        // resident solves that take step items
@@ -948,18 +964,25 @@ class Server {
         if (!eng) {
           eng.reset(new Engine(c_, c_.max_slots));
           eng->this_is_serving_ = true;
+          eng->newcomers = [this] {
+            std::lock_guard<std::mutex> lk(m_);
+            return !full_ && !queue_.empty();
+          };
           rc = eng->init();
         }
         // admission: FIFO while a slot is free and the footprint fits
+        full_ = false;
         while (rc == CG_OK) {
           Job* j = nullptr;
           {
             std::lock_guard<std::mutex> lk(m_);
-            if (stopping_ || queue_.empty() || !eng->has_free()) break;
+            full_ = stopping_ || !eng->has_free();
+            if (full_ || queue_.empty()) break;
             j = queue_.front();
           }
           const int a = eng->admit(j);
-          if (a == CG_E_NOMEM && eng->active() > 0) break;
+          full_ = a == CG_E_NOMEM && eng->active() > 0;
+          if (full_) break;
           std::lock_guard<std::mutex> lk(m_);
           queue_.pop_front();
           if (a != CG_OK) {
@@ -990,6 +1013,7 @@ class Server {
   std::deque<Job*> queue_;
   std::unordered_map<uint64_t, Job*> jobs_;
   bool stopping_ = false;
+  bool full_ = false;  // nothing more can be admitted for now (the loop's thread only)
   uint64_t next_ticket_ = 1;
 };
 

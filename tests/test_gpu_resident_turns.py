@@ -1,5 +1,6 @@
 """Contexts whose solves run in the resident loop share the device by launches:
-a long solve of one does not keep another's from the device until it ends."""
+a long solve of one does not keep another's from the device until it ends.  In
+one server the other requests go on beside a launch of the loop."""
 import threading
 import time
 
@@ -68,3 +69,20 @@ def test_short_solves_beside_a_long_one(torch, how):
             assert beside
         assert "resident_abandoned" not in a.cg_kernel_stats()
         assert "resident_abandoned" not in c.cg_kernel_stats()
+
+
+def test_small_requests_beside_a_launch(torch):
+    """Small requests, one after the other, do not each wait for a whole launch
+    of the loop: on average for less than 160 of a large solve's iterations (a
+    launch has 256 when nothing else arrives)."""
+    big, small = rhs(torch, 1024, 1024), rhs(torch, 12, 12, 2)
+    with cg.Context(device=0, arena_bytes=1 << 30) as c:
+        xb, x = torch.zeros_like(big), torch.zeros_like(small)
+        torch.cuda.synchronize()
+        t = c.cg_submit(cg.make_problem(big, xb, 1024, 1024, tol=0.0, maxit=20000))
+        n = 0
+        while c.cg_poll(t)[0] == cg.CG_PENDING:
+            served(c, small, x, dict(tol=0.0, maxit=1))
+            n += 1
+        print("served", n, c.cg_kernel_stats(), flush=True)
+        assert n > 20000 // 160

@@ -50,6 +50,7 @@ struct Job {
   int slot = -1;
   enum { kStep, kLoop } mode = kStep;  // in kLoop the resident launches advance it
   int kind = -1;   // kind of its resident loop; -1: none
+  int passed = 0;  // kLoop: launches since its last that had no room for it
   int parity = 0;  // kLoop: state and partials lie in the buffers of this parity
   int64_t steps_cap = 0;
   bool finished = false;
@@ -405,12 +406,14 @@ class Engine {
     return most;
   }
 
-  // Launches the next iterations of the solves in the loop: in order of
-  // admission, as many as the device holds at once, near where one XCD holds
-  // them.  Those that need all XCDs come first (the longest, and they would
-  // wait until the others leave room on every XCD).  Few strips per wavefront make an iteration short (300 x 190 classic
-  // on one XCD 3.3 us with one or two, 3.6 with four), many let more solves in:
-  // as many as it takes for all waiting solves to fit.
+  // Launches the next iterations of the solves in the loop, as many as the
+  // device holds at once, near where one XCD holds them.  First those that
+  // kLoopPatience launches have left out, the longest waiting foremost: every
+  // solve gets its turn, whatever else arrives.  Then those that need all XCDs
+  // (they would wait until the others leave room on every XCD), then the rest,
+  // each in order of admission.  Few strips per wavefront make an iteration
+  // short (300 x 190 classic on one XCD 3.3 us with one or two, 3.6 with four),
+  // many let more solves in: as many as it takes for all waiting solves to fit.
   int launch_loop() {
     loop_run_.clear();
     std::vector<Job*> wait;
@@ -421,6 +424,9 @@ class Engine {
       return !loop_fits(j, 1, true) && !loop_fits(j, 2, true) && !loop_fits(j, 4, true);
     };
     std::sort(wait.begin(), wait.end(), [&](const Job* a, const Job* b) {
+      const int pa = a->passed < kLoopPatience ? 0 : a->passed;
+      const int pb = b->passed < kLoopPatience ? 0 : b->passed;
+      if (pa != pb) return pa > pb;
       return far(a) != far(b) ? far(a) : a->t_admit < b->t_admit;
     });
     int least = 1;
@@ -462,7 +468,9 @@ class Engine {
         for (int x = 0; x < loop_xcds_; ++x) room += loop_room_ - used[x];
         if (loop_wgs(j, k) <= room) h = k;
       }
+      ++j->passed;
       if (!h) continue;  // no room this time
+      j->passed = 0;
       const int id = (int)loop_run_.size(), n = loop_wgs(j, h);
       hd[id] = resident_solve(j->w, j->w.S[j->parity], j->w.part[j->parity],
                               kLoopBudget >> loop_short_, c_.resident_spin);
@@ -596,6 +604,7 @@ class Engine {
         if (j->kind >= 0 && loops(s)) {
           // held: the loop takes it from here
           j->mode = Job::kLoop;
+          j->passed = 0;
           j->parity = (step_ - h_slots_[i].admit_step) & 1;
           --step_jobs_;
           dirty_ = true;
@@ -811,6 +820,7 @@ class Engine {
   // the resident loop: work-groups an XCD holds at once (0: no loop), and the
   // launch in flight (its solves and tables)
   static constexpr int kLoopBudget = 256;  // iterations a launch
+  static constexpr int kLoopPatience = 3;  // launches a solve is left out of
   int loop_short_ = 0;  // halvings of the next launch's iterations
   int loop_xcds_ = 8, loop_room_ = 0;
   hipEvent_t loop_ev_ = nullptr;

@@ -1,6 +1,7 @@
 """Batches and served requests whose iterations run in the resident loop, where
 the engine has to move a solve between the loop and its steps."""
 import os
+import time
 
 import numpy as np
 import pytest
@@ -71,3 +72,34 @@ def test_no_room_for_the_tables_after_a_launch(torch, variant):
             assert res[0].iterations == ref.iterations and res[0].status == ref.status
             assert res[0].rel_res_true == ref.rel_res_true
             np.testing.assert_array_equal(x.cpu().numpy(), ref_x)
+
+
+@pytest.mark.parametrize("variant", [0, 1])
+def test_a_small_solve_among_large_ones_gets_its_turn(torch, variant):
+    """A request that one XCD holds is served long before requests that take
+    the whole device, and that came first, are done; and one of those before
+    the small requests that keep coming are."""
+    n, m = 1024, 200
+    big, small = rhs(torch, n, n), rhs(torch, m, m)
+    xs = [torch.zeros_like(big) for _ in range(4)]
+    x = torch.zeros_like(small)
+    torch.cuda.synchronize()
+    with context(arena=4 << 30) as c:
+        def submit(b, x, side, **kw):
+            return c.cg_submit(cg.make_problem(b, x, side, side, variant=variant, **kw))
+
+        left = [submit(big, y, n, tol=1e-6, maxit=4000) for y in xs]
+        time.sleep(0.005)
+        t = submit(small, x, m, tol=0.0, maxit=300)
+        while c.cg_poll(t)[0] == cg.CG_PENDING:
+            pass
+        left = [t for t in left if c.cg_poll(t)[0] == cg.CG_PENDING]
+        print("small solve done, large ones left:", len(left), flush=True)
+        assert len(left) == 4
+        turns = 0
+        while left:
+            t = submit(small, x, m, tol=0.0, maxit=300)
+            while c.cg_poll(t)[0] == cg.CG_PENDING:
+                left = [q for q in left if c.cg_poll(q)[0] == cg.CG_PENDING]
+            turns += 1
+            assert turns < 1000

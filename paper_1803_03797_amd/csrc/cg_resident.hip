@@ -37,9 +37,11 @@
 //
 // Every wait is bounded: all work-groups of a solve must be on the device
 // together, which the host ensures by the size of the launch, but another
-// process may hold the compute units.  A work-group that sees no progress for
-// `spin` polls marks the solve as abandoned and ends; the others then do the
-// same, and the host runs the solve by passes.
+// process, or another stream's long kernel, may hold the compute units.  A
+// work-group that sees no progress for `spin` polls marks the solve as abandoned
+// and ends; the others, waiting in the same meeting, then do the same, and the
+// host runs the solve by passes.  (Looking at the mark while polling took 2 % of
+// an iteration and ended a wait no sooner.)
 //
 // Results are those of the passes, bit for bit: the same tiles, lane order,
 // butterflies, tile order and scalar recurrences.  x is updated every

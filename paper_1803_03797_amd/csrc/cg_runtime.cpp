@@ -857,6 +857,7 @@ Resident resident_of(const Ctx& c, const Plan& pl) {
   Resident r;
   if (!c.resident_on || c.prof || pl.wg || pl.precond || pl.vc || pl.rr_period || pl.g.plane)
     return r;
+  if (c.resident_after > 0.0 && now_s() < c.resident_after) return r;
   if (!pl.refined && pl.fp32g) return r;  // classic FP64 pinned to 4 columns per lane
   r.kind = pl.refined ? 2 : pl.variant;
   if (pl.g.tiles > kResMaxTiles) return r;
@@ -912,6 +913,21 @@ void count_resident(Ctx& c, int kind, int rows, int strips, bool near) {
   c.prof_add(name, 0.0, 0.0, 1);
 }
 
+// A solve is abandoned where something else holds the device (another process
+// in its own resident loop, a long kernel of another stream): a wait of some tens
+// of milliseconds, and its iterations from the start.  What holds it is likely to
+// stay, so the context's solves run by passes for a second, or twice the last
+// pause (a minute at most) if the first launch after it was abandoned again.
+void resident_outcome(Ctx& c, int abandoned) {
+  if (!abandoned) {
+    c.resident_pause = 0.0;
+    return;
+  }
+  c.prof_add(kResidentAbandoned, 0.0, 0.0, abandoned);
+  c.resident_pause = std::min(60.0, std::max(1.0, 2.0 * c.resident_pause));
+  c.resident_after = now_s() + c.resident_pause;
+}
+
 constexpr int kAbandoned = 1;  // run_resident: the solve is to be run by passes
 
 // Runs a solve whose next pass begins an odd iteration (K_CG1, K_PCG, K_CG1F)
@@ -930,6 +946,7 @@ static int run_resident(Ctx& c, Work& w, const Resident& r, State& s) {
     if (rc) return rc;
     uint64_t dead;
     memcpy(&dead, flag, sizeof(dead));
+    resident_outcome(c, dead != 0 ? 1 : 0);
     if (dead) return kAbandoned;
     if (s.status != ST_RUNNING) return CG_OK;
   }
@@ -1139,7 +1156,6 @@ int Ctx::solve(const cg_problem* p, cg_result* res) {
                   : solve_tiled(c, w, p, s, r);
   if (rc == kAbandoned && !w.pl.wg) {
     // the device was not free for all of the solve's work-groups at once
-    c.prof_add(kResidentAbandoned, 0.0, 0.0, 1);
     if ((rc = stage_in(c, w, p))) return rc;
     rc = solve_tiled(c, w, p, s, Resident());
   }

@@ -113,6 +113,8 @@ Resident resident_of(const Ctx& c, const Plan& pl);
 // The solve as it stands, for a launch of `budget` iterations; numbers its meetings.
 cgk::ResSolve resident_solve(Work& w, const cgk::State* st, const double* part, int budget,
                              int spin);
+// After a launch: counts its abandoned solves, and pauses the loop if there are any.
+void resident_outcome(Ctx& c, int abandoned);
 // Counts a launch of the loop in the context's statistics; an abandoned solve
 // is counted under kResidentAbandoned.
 void count_resident(Ctx& c, int kind, int rows, int strips, bool near);
@@ -182,7 +184,10 @@ struct Ctx {
   int serve_chunk = 8;         // serving: steps between admissions
   bool resident_on = true;     // iteration loops of mid-size solves in one launch
   int resident_budget = 1024;  // ... iterations of one launch
-  int resident_spin = 1 << 20; // ... polls before a wait is given up
+  int resident_spin = 1 << 16; // ... polls before a wait is given up (some tens of ms)
+  double resident_after = 0.0; // ... not before this time: a solve was abandoned
+  double resident_pause = 0.0; // ... and the pause that followed (0: none, or a launch
+                               // has gone through since)
   int resident_strips = 0;     // ... strips per wavefront (0: by the grid)
   bool resident_near = true;   // ... on one XCD where it fits
   int cheb_item_div = 1;       // Chebyshev items per pass: resident work-groups / this

@@ -435,10 +435,12 @@ class Engine {
       for (const Job* j : wait) n += loop_wgs(j, least);
       if (n <= (int64_t)loop_xcds_ * loop_room_ * 3 / 4) break;
     }
-    loop_mem_ = (char*)c_.arena.alloc(loop_desc_bytes() + loop_wgs_bytes() +
-                                      (size_t)n_ * sizeof(State));
+    if (now_s() >= c_.resident_after)
+      loop_mem_ = (char*)c_.arena.alloc(loop_desc_bytes() + loop_wgs_bytes() +
+                                        (size_t)n_ * sizeof(State));
     if (!loop_mem_) {
-      // no room for the launch's tables: these solves go on by steps
+      // the loop pauses, or the arena has no room for the launch's tables:
+      // these solves go on by steps
       for (Job* j : wait)
         if (int rc = to_steps(j, false)) return rc;
       return CG_OK;
@@ -535,6 +537,9 @@ class Engine {
     if (e != hipSuccess) return CG_E_DEVICE;
     int rc = CG_OK;
     const State* hs = (const State*)(h_loop_ + loop_desc_bytes() + loop_wgs_bytes());
+    int abandoned = 0;
+    for (size_t i = 0; i < loop_run_.size(); ++i) abandoned += hs[i].pad_ != 0;
+    resident_outcome(c_, abandoned);
     for (size_t i = 0; i < loop_run_.size() && rc == CG_OK; ++i) {
       Job* j = loop_run_[i];
       if (hs[i].pad_) rc = restart(j);
@@ -568,7 +573,6 @@ class Engine {
 
   // A solve that its launch abandoned: from the start, by steps.
   int restart(Job* j) {
-    c_.prof_add(kResidentAbandoned, 0.0, 0.0, 1);
     j->kind = -1;
     j->mode = Job::kStep;
     ++step_jobs_;

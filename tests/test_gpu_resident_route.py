@@ -2,6 +2,7 @@
 The loop and the passes give the same bits, so only the context's statistics
 tell them apart."""
 import os
+import time
 
 import numpy as np
 import pytest
@@ -144,3 +145,31 @@ def test_batches_loop(torch):
         for a, b in zip(batch(c), want):
             np.testing.assert_array_equal(a, b)
         assert 1 <= loops(c)["abandoned"] <= len(shapes)
+
+
+@pytest.mark.parametrize("batch", [0, 1])
+def test_the_loop_pauses_after_an_abandoned_solve(torch, batch):
+    """What held the device is likely to stay: the next solves run by passes,
+    without waiting for it each, until a pause of a second is over."""
+    nx, ny = 640, 512
+    b = rhs(torch, nx, ny)
+
+    def run(c):
+        x = torch.zeros_like(b)
+        p = cg.make_problem(b, x, nx, ny, tol=0.0, maxit=50)
+        if batch:
+            c.cg_solve_batch([p])
+        else:
+            c.cg_solve(p)
+        return x.cpu().numpy()
+
+    with context(CG_RESIDENT=0) as c:
+        want = run(c)
+    with context(CG_RESIDENT_SPIN=1) as c:
+        for n in (1, 1, 1):
+            np.testing.assert_array_equal(run(c), want)
+            assert c.cg_kernel_stats()["resident_abandoned"]["launches"] == n
+        time.sleep(1.1)
+        for n in (2, 2):
+            np.testing.assert_array_equal(run(c), want)
+            assert c.cg_kernel_stats()["resident_abandoned"]["launches"] == n

@@ -1327,7 +1327,11 @@ int Ctx::mul_probe(int rounds, int reps, double* seconds, double* ops) {
 // occupancy limit and 1/2, 1/3, 1/4 of it, capped by the tile count) x
 // columns per lane (2 or 4 for classic FP64).  Each candidate runs a short
 // fixed-iteration solve (tol = 0) twice; the score is the HIP-event time of
-// the iteration kernels of the second run per iteration.
+// the iteration kernels of the second run per iteration.  Where a candidate
+// runs its iterations in the resident loop (which has no passes to time, and
+// most shapes do not fit) the score is the wall time of longer solves as a
+// caller runs them, the best of three: 1024^2 classic by passes 17 us an
+// iteration whatever the shape, in the loop 7.4.
 int Ctx::tune(int nx, int ny, int variant, int precision) {
   Ctx& c = *this;
   cg_problem p;
@@ -1368,18 +1372,49 @@ int Ctx::tune(int nx, int ny, int variant, int precision) {
   else names = {"stencil_dot", "update_norm", "update_norm_nx"};
   std::vector<int> cpls = {0};
   if (!fp32g && variant == CG_VARIANT_CLASSIC) cpls = {2, 4};
-  const bool save_prof = prof;
-  const auto save_stats = stats;
-  prof = true;
-  double best = 1e30;
   // the shape the solve takes unpinned is the fallback and the first
   // candidate, so the pick is never slower than it by the tuner's measure
   pins.erase(k);
   Pin bestp{unpinned_rows(&p, fp32g), plan(&p).grid, 0};
+  std::vector<Pin> cands = {bestp};
+  for (int cpl : cpls) {
+    const int geo4 = fp32g || cpl == 4;
+    const int kind = fp32g ? K_CG2F : (variant == CG_VARIANT_PIPELINED ? K_PCG : K_CG2);
+    const int cap = std::max(8, pass_max_blocks_per_cu(kind, geo4) * num_cu);
+    for (int rows : {2, 4, 8, 16, 32, 64}) {
+      const Geo g = make_geo(nx, ny, geo4, rows);
+      if (rows > 4 * ((ny + 3) / 4)) continue;
+      std::vector<int> grids;
+      for (int div : {1, 2, 3, 4}) {
+        int gsz = (int)round_up((size_t)std::max(8, cap / div), 8);
+        gsz = std::min(gsz, (int)round_up((size_t)g.tiles, 8));
+        if (std::find(grids.begin(), grids.end(), gsz) == grids.end()) grids.push_back(gsz);
+      }
+      for (int gsz : grids) cands.push_back(Pin{rows, gsz, cpl});
+    }
+  }
+  const bool save_prof = prof;
+  const auto save_stats = stats;
+  prof = false;
+  bool whole = false;
+  for (const Pin& pin : cands) {
+    pins[k] = pin;
+    whole = whole || resident_of(*this, plan(&p)).wgs > 0;
+  }
+  prof = !whole;
+  if (whole) p.maxit = 200;
   auto score = [&](const Pin& pin, double& t) {
     pins[k] = pin;
     cg_result r;
     if (solve(&p, &r) < 0) return false;  // warms graphs and caches
+    if (whole) {
+      t = 1e30;
+      for (int i = 0; i < 3; ++i) {
+        if (solve(&p, &r) < 0) return false;
+        t = std::min(t, r.device_seconds / std::max(1, r.iterations));
+      }
+      return true;
+    }
     stats.clear();
     if (solve(&p, &r) < 0) return false;
     t = 0.0;
@@ -1394,32 +1429,13 @@ int Ctx::tune(int nx, int ny, int variant, int precision) {
     t /= (double)p.maxit;  // per iteration (tol = 0: exactly maxit of them)
     return launches > 0;
   };
-  {
+  double best = 1e30;
+  for (const Pin& pin : cands) {
     double t;
-    if (score(bestp, t)) best = t;
-  }
-  for (int cpl : cpls) {
-    const int geo4 = fp32g || cpl == 4;
-    const int kind = fp32g ? K_CG2F : (variant == CG_VARIANT_PIPELINED ? K_PCG : K_CG2);
-    const int cap = std::max(8, pass_max_blocks_per_cu(kind, geo4) * num_cu);
-    for (int rows : {2, 4, 8, 16, 32, 64}) {
-      const Geo g = make_geo(nx, ny, geo4, rows);
-      if (rows > 4 * ((ny + 3) / 4)) continue;
-      std::vector<int> grids;
-      for (int div : {1, 2, 3, 4}) {
-        int gsz = (int)round_up((size_t)std::max(8, cap / div), 8);
-        gsz = std::min(gsz, (int)round_up((size_t)g.tiles, 8));
-        if (std::find(grids.begin(), grids.end(), gsz) == grids.end()) grids.push_back(gsz);
-      }
-      for (int gsz : grids) {
-        double t;
-        if (!score(Pin{rows, gsz, cpl}, t)) continue;
-        if (t < best) {
-          best = t;
-          bestp = Pin{rows, gsz, cpl};
-        }
-      }
-    }
+    // wall times of equal solves differ by a few percent
+    if (!score(pin, t) || t >= (whole ? 0.97 : 1.0) * best) continue;
+    best = t;
+    bestp = pin;
   }
   prof = save_prof;
   stats = save_stats;
@@ -1429,7 +1445,11 @@ int Ctx::tune(int nx, int ny, int variant, int precision) {
 }
 
 // The tune cache is one JSON object per line:
-//   {"nx": 4096, "ny": 4096, "fp32": 0, "rows": 32, "grid": 1024, "cpl": 2}
+//   {"arch": "gfx950", "hip": 70051831, "nx": 4096, "ny": 4096, "fp32": 0, "variant": 0,
+//    "rows": 32, "grid": 1024, "cpl": 2, "loop": 1}
+// "loop": the shapes were measured against the resident loop.  A line without it
+// says only which shape had the fastest passes, so it is ignored for a grid whose
+// iterations run in the loop unless a shape is pinned.
 void Ctx::load_tune_cache() {
   if (tune_path.empty()) return;
   FILE* f = fopen(tune_path.c_str(), "r");
@@ -1444,8 +1464,22 @@ void Ctx::load_tune_cache() {
                "\"variant\": %d, \"rows\": %d, \"grid\": %d, \"cpl\": %d}",
                ar, &hv, &nx, &ny, &fp, &var, &rows, &grid, &cpl) == 9 &&
         arch == ar && hv == hip_version && nx > 0 && ny > 0 && rows > 0 && rows <= 4096 &&
-        grid >= 0 && (var == 0 || var == 1) && (cpl == 0 || cpl == 2 || cpl == 4))
-      pins[key(nx, ny, fp, var)] = Pin{rows, grid, cpl};
+        grid >= 0 && (var == 0 || var == 1) && (cpl == 0 || cpl == 2 || cpl == 4)) {
+      const uint64_t k = key(nx, ny, fp, var);
+      if (!strstr(line, "\"loop\": 1")) {
+        cg_problem q;
+        memset(&q, 0, sizeof(q));
+        q.nx = nx;
+        q.ny = ny;
+        q.variant = (cg_variant)var;
+        q.precision = fp ? CG_PREC_FP32_REFINED : CG_PREC_FP64;
+        const auto was = pins.extract(k);
+        const bool loops = resident_of(*this, plan(&q)).wgs > 0;
+        if (loops && !was.empty()) pins[k] = was.mapped();
+        if (loops) continue;
+      }
+      pins[k] = Pin{rows, grid, cpl};
+    }
   }
   fclose(f);
 }
@@ -1457,7 +1491,7 @@ void Ctx::save_tune_cache() {
   for (auto& kv : pins)
     fprintf(f,
             "{\"arch\": \"%s\", \"hip\": %d, \"nx\": %d, \"ny\": %d, \"fp32\": %d, "
-            "\"variant\": %d, \"rows\": %d, \"grid\": %d, \"cpl\": %d}\n",
+            "\"variant\": %d, \"rows\": %d, \"grid\": %d, \"cpl\": %d, \"loop\": 1}\n",
             arch.c_str(), hip_version, (int)(kv.first >> 34),
             (int)((kv.first >> 2) & 0xffffffff), (int)(kv.first & 1), (int)((kv.first >> 1) & 1),
             kv.second.rows, kv.second.grid, kv.second.cpl);

@@ -260,7 +260,9 @@ struct ResWg {
   int32_t solve, wg;
 };
 
-constexpr int kResMaxTiles = 1536;  // tiles of a resident solve
+// Tiles of a resident solve.  Unpinned grids have strips of 2 rows up to 1.5 x
+// (1024 + tiles across) tiles, of 3 rows up to 1366, of 4 up to 1280.
+constexpr int kResMaxTiles = 1600;
 
 // Fixed-point variant (cg_fixed.hip): values are Q20.30 held as int64 counts
 // of 2^-30 in [-2^49, 2^49 - 1] (the paper's 50-bit format with 20 integer

@@ -569,15 +569,20 @@ __device__ __forceinline__ void clip(Row<T, CPL>& v, const Place& p, int i) {
 
 // The lane's sums over the rows of strip s in the order of the passes: down
 // the strip, or up it for the odd strips of a tile (ALT, the classic passes).
+// With an odd H the direction depends on the wavefront; the empty asm keeps the
+// two directions apart (merged, they index the rows at run time, which puts them
+// in scratch memory).
 template <int R, int H, bool ALT, class F>
 __device__ __forceinline__ void strip_rows(const Place& p, int s, F f) {
   const bool up = ALT && (((p.wave * H + s) & 1) != 0);
   if (up) {
 #pragma unroll
     for (int i = R - 1; i >= 0; --i) f(s * R + i);
+    if (H & 1) asm volatile("; up");
   } else {
 #pragma unroll
     for (int i = 0; i < R; ++i) f(s * R + i);
+    if (H & 1) asm volatile("; down");
   }
 }
 
@@ -885,22 +890,17 @@ __device__ __forceinline__ void resident(const ResSolve* a, int wg, char* raw) {
   else resident_cg<float, 4, R, H, NEAR>(a, wg, raw);
 }
 
-constexpr size_t lds_bytes(int nr) {
-  return nr == 2 ? sizeof(ResLds<double, 2, 2>)
-         : nr == 4 ? sizeof(ResLds<double, 2, 4>)
-         : nr == 8 ? sizeof(ResLds<double, 2, 8>) : sizeof(ResLds<double, 2, 16>);
+template <int KIND, int NR>
+constexpr size_t lds_bytes() {
+  return KIND == 2 ? sizeof(ResLds<float, 4, NR>) : sizeof(ResLds<double, 2, NR>);
 }
-static_assert(sizeof(ResLds<float, 4, 16>) <= lds_bytes(16) &&
-                  sizeof(ResLds<float, 4, 8>) <= lds_bytes(8) &&
-                  sizeof(ResLds<float, 4, 2>) <= lds_bytes(2),
-              "one size for both types");
 
 // KIND: 0 classic FP64, 1 pipelined FP64, 2 the refinement's inner solve.
 // One solve: work-group blockIdx.x, near every eighth block's (block b runs on
 // XCD b % 8).
 template <int KIND, int R, int H, bool NEAR>
 __global__ __launch_bounds__(kGroup) void k_resident(ResSolve one) {
-  __shared__ alignas(16) char raw[lds_bytes(R * H)];
+  __shared__ alignas(16) char raw[lds_bytes<KIND, R * H>()];
   int wg = blockIdx.x;
   if (NEAR) {
     if (wg & 7) return;
@@ -929,7 +929,8 @@ __device__ __attribute__((noinline)) void resident_call(const ResSolve* a, int w
 // compute unit (at most 256 registers): what the host counts by.
 __global__ __launch_bounds__(kGroup, 2) void k_resident_many(const ResSolve* many,
                                                              const ResWg* wgs) {
-  __shared__ alignas(16) char raw[lds_bytes(8)];
+  __shared__ alignas(16) char raw[lds_bytes<0, 8>()];
+  static_assert(lds_bytes<2, 8>() <= lds_bytes<0, 8>(), "one size for both types");
   const ResWg e = wgs[blockIdx.x];
   const int i = __builtin_amdgcn_readfirstlane(e.solve);
   const int wg = __builtin_amdgcn_readfirstlane(e.wg);
@@ -959,7 +960,15 @@ __global__ void k_resident_states(const ResSolve* many, int n, State* out) {
   out[i] = s;
 }
 
-// The compiled shapes of one solve.
+// The compiled shapes of one solve.  Strips of 2 rows cover the grids of up to
+// about 1.5 times 1024 tiles.  Taller ones, which larger grids have, are there
+// for the binary32 inner solve (four vectors of half the bytes), with as many
+// strips as its registers take: of 3 rows 6 (1024 to 1366 tiles on 256
+// work-groups), of 4 rows 4 or, from 1025 tiles, 5 (19 registers spilled; up to
+// 1280 tiles).  us per iteration by passes / resident: 1792^2 21.2 / 9.3 (3
+// rows), 2047^2 26.2 / 10.4, 2048^2 24.2 / 8.7 (4 rows, 4 strips), 2049^2 26.4 /
+// 11.3 (5 strips), 2200^2 27.8 / 11.6.  Larger grids (from 2241^2) would need more
+// rows a wavefront than fit.
 using Kernel = void (*)(ResSolve);
 
 template <int KIND, bool NEAR>
@@ -967,8 +976,11 @@ Kernel kernel_h(int rows, int strips) {
   if (rows == 2 && strips == 1) return k_resident<KIND, 2, 1, NEAR>;
   if (rows == 2 && strips == 2) return k_resident<KIND, 2, 2, NEAR>;
   if (rows == 2 && strips == 4) return k_resident<KIND, 2, 4, NEAR>;
-  if constexpr (KIND == 2 && !NEAR)
+  if constexpr (KIND == 2 && !NEAR) {
+    if (rows == 3 && strips == 6) return k_resident<KIND, 3, 6, NEAR>;
     if (rows == 4 && strips == 4) return k_resident<KIND, 4, 4, NEAR>;
+    if (rows == 4 && strips == 5) return k_resident<KIND, 4, 5, NEAR>;
+  }
   return nullptr;
 }
 

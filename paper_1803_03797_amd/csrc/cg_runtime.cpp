@@ -852,7 +852,7 @@ ResidentTurn& resident_turn_of(int device) {
 // work-groups, an iteration with more strips: at most 192 work-groups where
 // the strips allow (pipelined 384^2, 144 / 72 work-groups: 3.24 / 3.52 us;
 // classic 512^2, 256 / 128 / 64: 6.82 / 5.28 / 5.51; classic 640 x 1000, 315 /
-// 160: 7.68 / 6.32), else the most strips.
+// 160: 7.68 / 6.32), else four strips, else the fewest that fit.
 Resident resident_of(const Ctx& c, const Plan& pl) {
   Resident r;
   if (!c.resident_on || c.prof || pl.wg || pl.precond || pl.vc || pl.rr_period || pl.g.plane)
@@ -862,7 +862,7 @@ Resident resident_of(const Ctx& c, const Plan& pl) {
   r.kind = pl.refined ? 2 : pl.variant;
   if (pl.g.tiles > kResMaxTiles) return r;
   for (int near = c.resident_near ? 1 : 0; near >= 0 && !r.wgs; --near)
-    for (int h : {1, 2, 4}) {
+    for (int h : {1, 2, 4, 5, 6}) {
       if (c.resident_strips && h != c.resident_strips) continue;
       const int cus = near ? c.num_cu / 8 : c.num_cu;
       const int per_cu = resident_blocks_per_cu(r.kind, pl.g.rows, h, near);
@@ -871,7 +871,7 @@ Resident resident_of(const Ctx& c, const Plan& pl) {
       r.strips = h;
       r.wgs = n;
       r.near = near;
-      if (near || n <= 192) break;
+      if (near || n <= 192 || h >= 4) break;
     }
   return r;
 }

@@ -60,8 +60,8 @@ def forms(torch, ctx, nx, ny, tol=0.0, maxit=20):
     return out
 
 
-# one XCD holds a solve or it takes them all; the grids after which the binary64
-# solves run by passes; grids that never loop (on chip)
+# one XCD holds a solve or it takes them all; the grids after which solves run by
+# passes; grids that never loop (on chip)
 ROUTES = [((129, 128), ["cg_2x1_near", "pcg_2x1_near", "cg_f32_2x1_near"]),
           ((300, 190), ["cg_2x1_near", "pcg_2x1_near", "cg_f32_2x1_near"]),
           ((384, 384), ["cg_2x2_near", "pcg_2x1_far", "cg_f32_2x1_near"]),
@@ -70,8 +70,16 @@ ROUTES = [((129, 128), ["cg_2x1_near", "pcg_2x1_near", "cg_f32_2x1_near"]),
           ((1024, 1024), ["cg_2x4_far", "pcg_2x4_far", "cg_f32_2x4_far"]),
           ((1025, 1024), ["cg_2x4_far", None, "cg_f32_2x4_far"]),
           ((1024, 1025), ["cg_2x4_far", None, "cg_f32_2x4_far"]),
-          ((1536, 1025), [None, None, "cg_f32_2x4_far"]),
-          ((1752, 1752), [None, None, "cg_f32_2x4_far"]),
+          ((1536, 1025), ["cg_2x4_far", None, "cg_f32_2x4_far"]),
+          ((1536, 1040), [None, None, "cg_f32_2x4_far"]),
+          ((1234, 1234), ["cg_2x4_far", None, "cg_f32_2x4_far"]),
+          ((1760, 1760), [None, None, "cg_f32_2x4_far"]),
+          ((1764, 1764), [None, None, "cg_f32_3x6_far"]),
+          ((2047, 2048), [None, None, "cg_f32_4x4_far"]),
+          ((2048, 2047), [None, None, "cg_f32_3x6_far"]),
+          ((2049, 2049), [None, None, "cg_f32_4x5_far"]),
+          ((2240, 2240), [None, None, "cg_f32_4x5_far"]),
+          ((2241, 2241), [None, None, None]),
           ((100, 100), [None, None, "cg_f32_2x1_near"])]
 
 
@@ -173,3 +181,41 @@ def test_the_loop_pauses_after_an_abandoned_solve(torch, batch):
         for n in (2, 2):
             np.testing.assert_array_equal(run(c), want)
             assert c.cg_kernel_stats()["resident_abandoned"]["launches"] == n
+
+
+def test_no_gap_in_the_refined_range(torch):
+    """Every refined square up to 2240 loops."""
+    with context() as c:
+        for n in list(range(150, 1700, 77)) + list(range(1700, 2241, 13)) + [2240]:
+            b = torch.ones(n, n, device="cuda", dtype=torch.float64)
+            loops(c)
+            c.solve(b, torch.zeros_like(b), n, n, tol=1e-8, maxit=4,
+                    precision=cg.CG_PREC_FP32_REFINED)
+            got = loops(c)
+            assert len(got) == 1 and "abandoned" not in got, (n, got)
+
+
+# tall strips: their first and last grid, ragged rows and columns, one tile
+# column and many, a last work-group of few strips
+TALL = [(1764, 1764, "3x6"), (2041, 1805, "3x6"), (250, 13001, "3x6"), (2048, 2047, "3x6"),
+        (4000, 1001, "3x6"), (2048, 2048, "4x4"), (1023, 4096, "4x4"), (2049, 2049, "4x5"),
+        (2240, 2240, "4x5"), (3001, 1403, "4x5"), (255, 16399, "4x5")]
+
+
+@pytest.mark.parametrize("nx,ny,form", TALL)
+def test_tall_strips_equal_the_passes(torch, nx, ny, form):
+    b, x0 = rhs(torch, nx, ny, nx), rhs(torch, nx, ny, ny)
+    kw = dict(precision=cg.CG_PREC_FP32_REFINED)
+    with context() as c, context(CG_RESIDENT_BUDGET=7) as s, context(CG_RESIDENT=0) as p:
+        for start, tol, maxit in ((None, 1e-3, 90), (x0, 1e-8, 41)):
+            print("tall", nx, ny, form, maxit, flush=True)
+            out = []
+            for ctx in (p, c, s):
+                loops(ctx)
+                x = torch.zeros_like(b)
+                rc, r = ctx.solve(b, x, nx, ny, x0=start, tol=tol, maxit=maxit, **kw)
+                assert list(loops(ctx)) == ([] if ctx is p else ["cg_f32_%s_far" % form])
+                out.append((rc, r.iterations, r.outer_iterations, r.rel_res_true, x.cpu().numpy()))
+            for o in out[1:]:
+                assert o[:4] == out[0][:4]
+                np.testing.assert_array_equal(o[4], out[0][4])

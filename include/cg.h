@@ -235,7 +235,9 @@ typedef struct {
   char name[32];
   int64_t launches;
   double seconds;           /* summed HIP-event time of the launches                 */
-  double bytes;             /* summed algorithmic HBM bytes of the launches          */
+  double bytes;             /* summed algorithmic HBM bytes of the launches (variable
+                               coefficients: four face values per unknown, though
+                               cells share theirs and a pass reads two)              */
 } cg_kstat;
 
 /* Creates a context on cfg->device.  CG_E_DEVICE when no usable GPU. */

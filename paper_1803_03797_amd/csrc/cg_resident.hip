@@ -975,7 +975,10 @@ template <int KIND, bool NEAR>
 Kernel kernel_h(int rows, int strips) {
   if (rows == 2 && strips == 1) return k_resident<KIND, 2, 1, NEAR>;
   if (rows == 2 && strips == 2) return k_resident<KIND, 2, 2, NEAR>;
-  if (rows == 2 && strips == 4) return k_resident<KIND, 2, 4, NEAR>;
+  // the pipelined solve of four strips takes a compute unit: what then fits one
+  // XCD fits it with two strips as well
+  if constexpr (KIND != 1 || !NEAR)
+    if (rows == 2 && strips == 4) return k_resident<KIND, 2, 4, NEAR>;
   if constexpr (KIND == 2 && !NEAR) {
     if (rows == 3 && strips == 6) return k_resident<KIND, 3, 6, NEAR>;
     if (rows == 4 && strips == 4) return k_resident<KIND, 4, 4, NEAR>;

@@ -48,7 +48,7 @@ int cg_solve(cg_ctx* ctx, const cg_problem* prob, cg_result* res) {
   if (rc) return rc;
   const cg_problem q = cgr::resolve_precision(*prob);
   Ctx* c = C(ctx);
-  std::lock_guard<std::recursive_mutex> lk(c->mu);
+  std::lock_guard<cgr::ContextLock> lk(c->mu);
   if (hipSetDevice(c->device) != hipSuccess) return CG_E_DEVICE;
   return c->solve(&q, res);
 }
@@ -67,7 +67,7 @@ int cg_solve_batch(cg_ctx* ctx, const cg_problem* probs, int32_t n, cg_result* r
     q[i] = cgr::resolve_precision(probs[i]);
   }
   Ctx* c = C(ctx);
-  std::lock_guard<std::recursive_mutex> lk(c->mu);
+  std::lock_guard<cgr::ContextLock> lk(c->mu);
   if (hipSetDevice(c->device) != hipSuccess) return CG_E_DEVICE;
   return c->solve_batch(q.data(), n, results);
 }
@@ -104,7 +104,7 @@ int cg_apply(cg_ctx* ctx, int32_t nx, int32_t ny, cg_memspace mem, const double*
   if (!ctx || nx < 1 || ny < 1 || !u || !y || (mem != CG_MEM_HOST && mem != CG_MEM_DEVICE))
     return CG_E_INVALID;
   Ctx* c = C(ctx);
-  std::lock_guard<std::recursive_mutex> lk(c->mu);
+  std::lock_guard<cgr::ContextLock> lk(c->mu);
   if (hipSetDevice(c->device) != hipSuccess) return CG_E_DEVICE;
   return c->apply_or_dot(cgk::K_APPLY, nx, ny, mem, u, nullptr, y, nullptr);
 }
@@ -115,7 +115,7 @@ int cg_dot(cg_ctx* ctx, int32_t nx, int32_t ny, cg_memspace mem, const double* a
       (mem != CG_MEM_HOST && mem != CG_MEM_DEVICE))
     return CG_E_INVALID;
   Ctx* c = C(ctx);
-  std::lock_guard<std::recursive_mutex> lk(c->mu);
+  std::lock_guard<cgr::ContextLock> lk(c->mu);
   if (hipSetDevice(c->device) != hipSuccess) return CG_E_DEVICE;
   return c->apply_or_dot(cgk::K_DOT, nx, ny, mem, a, b, nullptr, out);
 }
@@ -126,7 +126,7 @@ int cg_plan(cg_ctx* ctx, const cg_problem* prob, cg_plan_info* info) {
   if (prob->precision == CG_PREC_FIXED && !cgk::fixed_fits(prob->nx, prob->ny))
     return CG_E_INVALID;
   Ctx* c = C(ctx);
-  std::lock_guard<std::recursive_mutex> lk(c->mu);
+  std::lock_guard<cgr::ContextLock> lk(c->mu);
   const cg_problem q = cgr::resolve_precision(*prob);
   cgr::Plan pl = c->plan(&q);
   memset(info, 0, sizeof(*info));
@@ -167,7 +167,7 @@ int cg_tune(cg_ctx* ctx, int32_t nx, int32_t ny, cg_variant variant, cg_precisio
   if (precision == CG_PREC_FIXED) return CG_OK;  // one work-group, no tile shape
   if (precision != CG_PREC_FP64 && precision != CG_PREC_FP32_REFINED) return CG_E_INVALID;
   Ctx* c = C(ctx);
-  std::lock_guard<std::recursive_mutex> lk(c->mu);
+  std::lock_guard<cgr::ContextLock> lk(c->mu);
   if (hipSetDevice(c->device) != hipSuccess) return CG_E_DEVICE;
   return c->tune(nx, ny, variant, precision);
 }
@@ -179,7 +179,7 @@ int cg_pin_tile(cg_ctx* ctx, int32_t nx, int32_t ny, cg_precision precision, int
   if (cols_per_lane != 0 && cols_per_lane != 2 && cols_per_lane != 4) return CG_E_INVALID;
   if (precision == CG_PREC_FP32_REFINED && cols_per_lane == 2) return CG_E_INVALID;
   Ctx* c = C(ctx);
-  std::lock_guard<std::recursive_mutex> lk(c->mu);
+  std::lock_guard<cgr::ContextLock> lk(c->mu);
   // the shape is pinned for both variants (refined solves have one key)
   const int fp = precision == CG_PREC_FP32_REFINED;
   for (int v = 0; v < 2; ++v)
@@ -192,7 +192,7 @@ int cg_stream_probe(cg_ctx* ctx, int32_t pattern, size_t elems, int32_t reps, do
   if (!ctx || !seconds || !bytes || pattern < 0 || pattern > 7 || elems < 2 || reps < 1)
     return CG_E_INVALID;
   Ctx* c = C(ctx);
-  std::lock_guard<std::recursive_mutex> lk(c->mu);
+  std::lock_guard<cgr::ContextLock> lk(c->mu);
   if (hipSetDevice(c->device) != hipSuccess) return CG_E_DEVICE;
   return c->stream_probe(pattern, elems, reps, seconds, bytes);
 }
@@ -200,7 +200,7 @@ int cg_stream_probe(cg_ctx* ctx, int32_t pattern, size_t elems, int32_t reps, do
 int cg_mul_probe(cg_ctx* ctx, int32_t rounds, int32_t reps, double* seconds, double* ops) {
   if (!ctx || !seconds || !ops || rounds < 1 || reps < 1) return CG_E_INVALID;
   Ctx* c = C(ctx);
-  std::lock_guard<std::recursive_mutex> lk(c->mu);
+  std::lock_guard<cgr::ContextLock> lk(c->mu);
   if (hipSetDevice(c->device) != hipSuccess) return CG_E_DEVICE;
   return c->mul_probe(rounds, reps, seconds, ops);
 }
@@ -208,7 +208,7 @@ int cg_mul_probe(cg_ctx* ctx, int32_t rounds, int32_t reps, double* seconds, dou
 int cg_set_profiling(cg_ctx* ctx, int32_t on) {
   if (!ctx) return CG_E_INVALID;
   Ctx* c = C(ctx);
-  std::lock_guard<std::recursive_mutex> lk(c->mu);
+  std::lock_guard<cgr::ContextLock> lk(c->mu);
   c->prof = on != 0;
   return CG_OK;
 }
@@ -216,7 +216,7 @@ int cg_set_profiling(cg_ctx* ctx, int32_t on) {
 int cg_kernel_stats(cg_ctx* ctx, cg_kstat* out, int32_t max, int32_t* count, int32_t reset) {
   if (!ctx || !count || max < 0 || (max > 0 && !out)) return CG_E_INVALID;
   Ctx* c = C(ctx);
-  std::lock_guard<std::recursive_mutex> lk(c->mu);
+  std::lock_guard<cgr::ContextLock> lk(c->mu);
   *count = (int32_t)c->stats.size();
   int32_t i = 0;
   for (auto& kv : c->stats) {

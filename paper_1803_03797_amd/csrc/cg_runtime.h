@@ -2,9 +2,11 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <condition_variable>
 #include <map>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/cg.h"
@@ -163,6 +165,44 @@ int default_rows(int nx, int ny, int fp32g);
 
 class Server;  // serving scheduler (cg_serve.cpp)
 
+// The lock of a context: recursive, and handed over in order of arrival.  The
+// server's thread takes its context again right after each of its turns; an
+// ordinary mutex would let it do so before a waiting caller wakes up.
+class ContextLock {
+ public:
+  void lock() {
+    std::unique_lock<std::mutex> lk(m_);
+    if (depth_ && owner_ == std::this_thread::get_id()) {
+      ++depth_;
+      return;
+    }
+    const uint64_t turn = next_++;
+    cv_.wait(lk, [&] { return !depth_ && turn == now_; });
+    owner_ = std::this_thread::get_id();
+    depth_ = 1;
+  }
+  void unlock() {
+    {
+      std::lock_guard<std::mutex> lk(m_);
+      if (--depth_) return;
+      ++now_;
+    }
+    cv_.notify_all();
+  }
+  // Whether another thread waits for the holder, who asks.
+  bool wanted() {
+    std::lock_guard<std::mutex> lk(m_);
+    return next_ > now_ + 1;
+  }
+
+ private:
+  std::mutex m_;
+  std::condition_variable cv_;
+  std::thread::id owner_;
+  int depth_ = 0;
+  uint64_t next_ = 0, now_ = 0;
+};
+
 struct Ctx {
   int device = 0;
   int num_cu = 256;
@@ -175,7 +215,7 @@ struct Ctx {
   Arena arena;
   int max_slots = 256;
   std::string tune_path;
-  std::recursive_mutex mu;
+  ContextLock mu;
   char* host_state = nullptr;  // pinned staging for state words
   int graph_chunk = 32;        // iterations per captured chunk; 0 = plain launches
   int wg_max_dof = 16384;      // whole-solve-in-one-work-group threshold (FP64)

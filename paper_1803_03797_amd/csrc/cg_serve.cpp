@@ -519,16 +519,16 @@ class Engine {
     loop_run_.clear();
   }
 
-  // Nothing to do beside the launch in flight: waits for its end, or a
-  // newcomer, a millisecond at most (the context is the caller's meanwhile).
+  // Nothing to do beside the launch in flight: waits for its end, a newcomer, or
+  // another caller of the context.
   int wait_loop() {
-    for (const double t0 = now_s(); now_s() - t0 < 1e-3;) {
+    for (;;) {
       const hipError_t e = hipEventQuery(loop_ev_);
-      if (e == hipSuccess || (e == hipErrorNotReady && newcomers && newcomers())) return CG_OK;
+      if (e == hipSuccess) return CG_OK;
       if (e != hipErrorNotReady) return CG_E_DEVICE;
+      if (c_.mu.wanted() || (newcomers && newcomers())) return CG_OK;
       std::this_thread::yield();
     }
-    return CG_OK;
   }
 
   // The launch has ended: moves the solves that it has brought to a stop back
@@ -972,7 +972,7 @@ class Server {
       }
       done.clear();
       {
-        std::lock_guard<std::recursive_mutex> ck(c_.mu);
+        std::lock_guard<ContextLock> ck(c_.mu);
         if (hipSetDevice(c_.device) != hipSuccess) break;
         int rc = CG_OK;
         if (!eng) {
@@ -1015,7 +1015,7 @@ class Server {
       }
     }
     if (eng) {
-      std::lock_guard<std::recursive_mutex> ck(c_.mu);
+      std::lock_guard<ContextLock> ck(c_.mu);
       eng.reset();
     }
   }

@@ -86,3 +86,37 @@ def test_small_requests_beside_a_launch(torch):
             n += 1
         print("served", n, c.cg_kernel_stats(), flush=True)
         assert n > 20000 // 160
+
+
+def test_calls_on_a_context_that_serves(torch):
+    """The server's thread lets other callers of its context in between its
+    turns: solves (on chip, in the loop, in a batch) are done while a served
+    one goes on."""
+    big, mid, small = rhs(torch, 700, 700), rhs(torch, 300, 190, 2), rhs(torch, 33, 17, 3)
+    kw = dict(tol=0.0, maxit=40)
+
+    def calls(c):
+        x, y = torch.zeros_like(mid), torch.zeros_like(small)
+        u, v = torch.zeros_like(mid), torch.zeros_like(small)
+        solved(c, small, y, kw)
+        solved(c, mid, x, kw)
+        c.cg_solve_batch([cg.make_problem(mid, u, 300, 190, **kw),
+                          cg.make_problem(small, v, 33, 17, **kw)])
+        return [t.cpu().numpy() for t in (x, y, u, v)]
+
+    with cg.Context(device=0, arena_bytes=1 << 30, max_slots=8) as c:
+        want = calls(c)
+        xb = torch.zeros_like(big)
+        torch.cuda.synchronize()
+        t = c.cg_submit(cg.make_problem(big, xb, 700, 700, tol=0.0, maxit=40000))
+        time.sleep(0.01)
+        for _ in range(3):
+            for a, b in zip(calls(c), want):
+                np.testing.assert_array_equal(a, b)
+            assert c.cg_poll(t)[0] == cg.CG_PENDING
+            print("calls beside a served solve", flush=True)
+        while c.cg_poll(t)[0] == cg.CG_PENDING:
+            time.sleep(0.001)
+        ref = torch.zeros_like(big)
+        solved(c, big, ref, dict(tol=0.0, maxit=40000))
+        np.testing.assert_array_equal(xb.cpu().numpy(), ref.cpu().numpy())

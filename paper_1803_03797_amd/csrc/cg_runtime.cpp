@@ -843,6 +843,18 @@ ResidentTurn& resident_turn_of(int device) {
   return t[device & 63];
 }
 
+void resident_ended(int device, uint64_t number) {
+  ResidentTurn& t = resident_turn_of(device);
+  std::lock_guard<std::mutex> lk(t.m);
+  if (t.number == number) t.last = nullptr;
+}
+
+void resident_ended(int device, hipStream_t st) {
+  ResidentTurn& t = resident_turn_of(device);
+  std::lock_guard<std::mutex> lk(t.m);
+  if (t.last == st) t.last = nullptr;
+}
+
 // Whether the iteration loop of a solve runs resident, and in which form.
 // Near where the solve fits one XCD (at most three work-groups a compute
 // unit), with as few strips per wavefront as that takes: measured classic, us
@@ -936,13 +948,17 @@ static int run_resident(Ctx& c, Work& w, const Resident& r, State& s) {
   for (;;) {
     const ResSolve a = resident_solve(w, w.S[w.m & 1], w.part[w.m & 1], c.resident_budget,
                                       c.resident_spin);
-    HIPCHK(resident_turn(c.device, c.st, [&] {
+    uint64_t turn = 0;
+    HIPCHK(resident_turn(c.device, c.st, turn, [&] {
       return launch_resident(r.kind, w.pl.g.rows, r.strips, r.near, a, r.wgs, c.st);
     }));
     count_resident(c, r.kind, w.pl.g.rows, r.strips, r.near);
     char* flag = c.host_state + 2048;  // pinned, past the state and the coefficients
-    HIPCHK(hipMemcpyAsync(flag, w.sync, sizeof(uint64_t), hipMemcpyDeviceToHost, c.st));
-    int rc = read_state(c, w, s);
+    const hipError_t e =
+        hipMemcpyAsync(flag, w.sync, sizeof(uint64_t), hipMemcpyDeviceToHost, c.st);
+    const int rc = read_state(c, w, s);  // waits for the launch
+    resident_ended(c.device, turn);
+    HIPCHK(e);
     if (rc) return rc;
     uint64_t dead;
     memcpy(&dead, flag, sizeof(dead));
@@ -1554,6 +1570,8 @@ Ctx::~Ctx() {
   if (st) (void)hipStreamSynchronize(st);
   if (side) (void)hipStreamSynchronize(side);
   if (loop) (void)hipStreamSynchronize(loop);
+  resident_ended(device, st);
+  resident_ended(device, loop);
   for (auto& kv : graphs) (void)hipGraphExecDestroy(kv.second);
   for (auto& pr : pending) {
     (void)hipEventDestroy(pr.a);

@@ -100,12 +100,13 @@ struct Resident {
   bool near = false;  // all work-groups on one XCD
 };
 
-// The resident launch issued last on a device, and its stream (a context waits
-// for its streams before it destroys them).
+// The stream of a device's latest resident launch, unless that is known to have
+// ended (a context clears what names its streams before it destroys them).
 struct ResidentTurn {
   std::mutex m;
-  hipEvent_t done = nullptr;
   hipStream_t last = nullptr;
+  uint64_t number = 0;  // of the launch
+  hipEvent_t ended = nullptr;
 };
 ResidentTurn& resident_turn_of(int device);
 
@@ -123,23 +124,30 @@ void count_resident(Ctx& c, int kind, int rows, int strips, bool near);
 constexpr const char* kResidentAbandoned = "resident_abandoned";
 // Issues a resident launch (`launch`, on `st`) in its turn on the device: the
 // work-groups of a launch wait for each other, so two that both fit alone must
-// not share it.  The device itself waits for the launch before, one event a
-// device, and no lock is held meanwhile: launches of all contexts follow each
-// other in the order they were issued, each of a bounded number of iterations.
+// not share it.  The device itself waits for a launch of another stream that may
+// be in flight, and no lock is held meanwhile: launches of all contexts follow
+// each other in the order they were issued, each of a bounded number of
+// iterations.
 template <class F>
-hipError_t resident_turn(int device, hipStream_t st, F launch) {
+hipError_t resident_turn(int device, hipStream_t st, uint64_t& number, F launch) {
   ResidentTurn& t = resident_turn_of(device);
   std::lock_guard<std::mutex> lk(t.m);
   hipError_t e = hipSuccess;
-  if (!t.done) e = hipEventCreateWithFlags(&t.done, hipEventDisableTiming);
-  else if (t.last != st) e = hipStreamWaitEvent(st, t.done, 0);
-  if (e != hipSuccess) return e;
-  t.last = st;
-  e = launch();
-  if (e == hipSuccess) e = hipEventRecord(t.done, st);
-  if (e != hipSuccess) (void)hipStreamSynchronize(st);
+  if (t.last && t.last != st) {
+    if (!t.ended) e = hipEventCreateWithFlags(&t.ended, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventRecord(t.ended, t.last);
+    if (e == hipSuccess) e = hipStreamWaitEvent(st, t.ended, 0);
+  }
+  if (e == hipSuccess) e = launch();
+  if (e == hipSuccess) {
+    t.last = st;
+    number = ++t.number;
+  }
   return e;
 }
+// The host has waited for the launch of this number; for all of a stream's.
+void resident_ended(int device, uint64_t number);
+void resident_ended(int device, hipStream_t st);
 bool carve(Ctx& c, Work& w);
 int stage_in(Ctx& c, Work& w, const cg_problem* p);
 cgk::State initial_state(const cg_problem* p);

@@ -498,7 +498,7 @@ class Engine {
     State* hs = (State*)(h_loop_ + loop_desc_bytes() + loop_wgs_bytes());
     if (hipMemcpyAsync(loop_mem_, h_loop_, loop_desc_bytes() + (size_t)grid * sizeof(ResWg),
                        hipMemcpyHostToDevice, c_.loop) ||
-        resident_turn(c_.device, c_.loop, [&] {
+        resident_turn(c_.device, c_.loop, loop_turn_, [&] {
           return launch_resident_many((const ResSolve*)loop_mem_,
                                       (const ResWg*)(loop_mem_ + loop_desc_bytes()), grid,
                                       c_.loop);
@@ -534,6 +534,7 @@ class Engine {
   // The launch has ended: moves the solves that it has brought to a stop back
   // to the steps.
   int finish_loop(hipError_t e) {
+    resident_ended(c_.device, loop_turn_);
     if (e != hipSuccess) return CG_E_DEVICE;
     int rc = CG_OK;
     const State* hs = (const State*)(h_loop_ + loop_desc_bytes() + loop_wgs_bytes());
@@ -828,6 +829,7 @@ class Engine {
   int loop_short_ = 0;  // halvings of the next launch's iterations
   int loop_xcds_ = 8, loop_room_ = 0;
   hipEvent_t loop_ev_ = nullptr;
+  uint64_t loop_turn_ = 0;
   char* loop_mem_ = nullptr;  // not null: in flight
   char* h_loop_ = nullptr;
   std::vector<Job*> loop_run_;

@@ -161,9 +161,10 @@ void fill_result(const cgk::State& s, cg_result* res, double secs, bool refined)
 
 int validate(const cg_problem* p);
 // CG_PREC_AUTO's choice: FP64 below kAutoRefineDof unknowns, FP32-refined from
-// there (measured in batches of equal requests on the step engine: refinement
-// 0.81x FP64's solves/s at 128^2, 1.17-1.39x from 181^2 to 2048^2); any other
-// precision unchanged
+// there; any other precision unchanged.  The line was drawn where both ran by
+// steps (refinement 0.81x FP64's solves/s at 128^2, 1.17x at 181^2); in batches of
+// the resident loop refinement measures 0.71x at 128^2, 0.96x at 181^2, 1.14x at
+// 256^2 and 1.75x at 1024^2.  It stays: the choice decides a request's bits.
 constexpr int64_t kAutoRefineDof = 20480;
 cg_problem resolve_precision(const cg_problem& p);
 size_t footprint_of(const cg_problem* p);

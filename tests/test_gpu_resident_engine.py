@@ -88,9 +88,9 @@ def test_a_small_solve_among_large_ones_gets_its_turn(torch, variant):
         def submit(b, x, side, **kw):
             return c.cg_submit(cg.make_problem(b, x, side, side, variant=variant, **kw))
 
-        left = [submit(big, y, n, tol=1e-6, maxit=4000) for y in xs]
+        left = [submit(big, y, n, tol=0.0, maxit=6000) for y in xs]
         time.sleep(0.005)
-        t = submit(small, x, m, tol=0.0, maxit=300)
+        t = submit(small, x, m, tol=0.0, maxit=100)
         while c.cg_poll(t)[0] == cg.CG_PENDING:
             pass
         left = [t for t in left if c.cg_poll(t)[0] == cg.CG_PENDING]
@@ -98,7 +98,7 @@ def test_a_small_solve_among_large_ones_gets_its_turn(torch, variant):
         assert len(left) == 4
         turns = 0
         while left:
-            t = submit(small, x, m, tol=0.0, maxit=300)
+            t = submit(small, x, m, tol=0.0, maxit=100)
             while c.cg_poll(t)[0] == cg.CG_PENDING:
                 left = [q for q in left if c.cg_poll(q)[0] == cg.CG_PENDING]
             turns += 1

@@ -251,7 +251,8 @@ int cg_solve(cg_ctx* ctx, const cg_problem* prob, cg_result* res);
 
 /* n independent solves on the device at once.  Every resident solve advances
  * by one CG pass per launch of a multi-solve step kernel (chunks of launches
- * replayed from a HIP graph); problems small enough for the on-chip solver
+ * replayed from a HIP graph); mid-size solves run their iterations in launches
+ * of many, beside the steps; problems small enough for the on-chip solver
  * (cg_plan_info.path 2) and fixed-point problems (path 3) run whole, one
  * work-group each, beside the steps.
  * Solves are admitted in order while their footprint fits the arena and a
